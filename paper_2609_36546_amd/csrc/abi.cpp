@@ -152,7 +152,7 @@ int verify_attn_paged(const void* q, const void* k_new, const void* v_new, void*
     return fail(IPDV_EWORKSPACE, "workspace of %zu bytes needed (got %zu)", pl.workspace_bytes,
                 workspace ? workspace_bytes : (size_t)0);
   ipdv::AttnLaunch L{q, k_new, v_new, k_cache, v_cache, page_table, max_pages_per_seq,
-                     ctx_lens, cu_q, seq_ids, n_seq, out, Hq, Hkv, D, page_size, num_pages,
+                     ctx_lens, cu_q, seq_ids, n_seq, max_q, out, Hq, Hkv, D, page_size, num_pages,
                      scale, dtype == IPDV_BF16, workspace};
   hipError_t e = ipdv::launch_verify_attn(L, pl, reinterpret_cast<hipStream_t>(hip_stream));
   if (e != hipSuccess) return hip_fail("verify_attn_paged launch", e);
@@ -178,7 +178,7 @@ int verify_attn_paged_noalloc(const void* q, const void* k_new, const void* v_ne
                 "holds %zu (use verify_attn_paged with a workspace)",
                 pl.workspace_bytes, (size_t)IPDV_NOALLOC_SCRATCH_BYTES);
   ipdv::AttnLaunch L{q, k_new, v_new, k_cache, v_cache, page_table, max_pages_per_seq,
-                     ctx_lens, cu_q, seq_ids, n_seq, out, Hq, Hkv, D, page_size, num_pages,
+                     ctx_lens, cu_q, seq_ids, n_seq, max_q, out, Hq, Hkv, D, page_size, num_pages,
                      scale, dtype == IPDV_BF16, nullptr};
   hipError_t e = ipdv::launch_verify_attn_noalloc(L, pl, reinterpret_cast<hipStream_t>(hip_stream));
   if (e != hipSuccess) return hip_fail("verify_attn_paged_noalloc", e);

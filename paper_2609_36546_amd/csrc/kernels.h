@@ -39,6 +39,7 @@ struct AttnPlan {
   int sub;             // keys per wave
   int chunk;           // keys per workgroup
   int max_chunks;      // chunk slots per group (padded to a multiple of 8)
+  int tile;            // unsplit tiles of 64 * tile query rows, 0: not taken (bf16, D = 128)
   int sk;              // full 64-row groups of 16-slot D = 128 pages: persistent stream-K kernel (bf16)
   int sk_qt;           // stream-K: 16-row tiles per wave (1: 64-row items, 2: 128-row items)
   int sk_n_qg;         // stream-K: items per (sequence, KV head)
@@ -57,7 +58,7 @@ struct AttnLaunch {
   const int32_t* ctx_lens;
   const int32_t* cu_q;
   const int32_t* seq_ids;
-  int n_seq;
+  int n_seq, max_q;
   void* out;
   int Hq, Hkv, D, page_size, num_pages;
   float scale;

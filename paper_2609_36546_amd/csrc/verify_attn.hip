@@ -11,7 +11,7 @@
 // attention streams every key, window or cached, the same way: by the
 // stream-K kernel itself (each workgroup writes the window positions inside
 // its own key blocks before it reads any), or by a small kernel ahead of the
-// register kernel.
+// register and tile kernels.
 //
 // Work decomposition.  The query rows of one (sequence, KV head) -- k window
 // positions x G = Hq/Hkv heads -- are packed position-major into groups of up
@@ -46,8 +46,10 @@
 // or 128 rows of one (sequence, KV head)), keys and values streamed through
 // an LDS ring with direct-to-LDS loads, and the key blocks of all items split
 // evenly between workgroups (stream-K); items split between workgroups are
-// merged by attn_combine_sk_kernel.  Both kernels share the block arithmetic
-// (attend_block) and the pool layouts.
+// merged by attn_combine_sk_kernel.  bf16 D = 128 heads with long windows or
+// short contexts take a third, verify_attn_tile_kernel: unsplit tiles of query
+// rows that walk all their keys (attn_plan has the rule).  The kernels share
+// the block arithmetic (attend_block) and the pool layouts.
 #include <algorithm>
 #include <mutex>
 
@@ -81,6 +83,8 @@ struct AttnParams {
   int page_size, log2ps, num_pages;
   int chunk, sub;     // keys per workgroup chunk / per wave
   int max_chunks, n_qg, n_seq;
+  int max_q;          // bound of the handled windows' rows
+  int al16;           // the window and cache arrays start on 16-byte boundaries
   float scale_log2;   // softmax scale * log2(e)
   int32_t* sk_start;  // stream-K: first block of every item (written by the attention kernel)
   int32_t* sk_ne;     // stream-K: non-empty items before every item (written with sk_start)
@@ -321,27 +325,76 @@ __device__ __forceinline__ void attend_block(const AttnParams& a, const FS& f,
 }
 
 // Append: the window's keys / values go to this verifier's pages at
-// positions L .. L+k-1 (one workgroup per sequence and KV head).
+// positions L .. L+k-1.  A workgroup takes kAppend positions of one sequence
+// and KV head (grid x: chunks from the 16-aligned position at or below L;
+// y: (sequence, head)).  Keys move in 16-byte chunks; values are turned from
+// [position][channel] to the pages' [channel][slot] through LDS, so that they
+// are stored in 16-byte runs of slots too (single elements only where a run
+// is cut by the window's ends).  One workgroup per (sequence, head) with
+// 2-byte strided stores took 384 us for eight prompts of 512-1024 tokens
+// (teacher heads), latency-bound on 32 workgroups; this takes 9 us.
+constexpr int kAppend = 64;
 template <typename DT, int D>
 __global__ __launch_bounds__(256) void append_window_kernel(AttnParams a) {
-  const int slot = blockIdx.x / a.Hkv, g = blockIdx.x % a.Hkv;
+  constexpr int EPL = 16 / (int)sizeof(DT);
+  constexpr int CPR = D / EPL;                 // 16-byte chunks per row
+  constexpr int LDP = D + 4 / (int)sizeof(DT); // LDS pitch: a row is an odd number of banks
+  typedef __attribute__((__vector_size__(16))) int i32x4;
+  const int slot = blockIdx.y / a.Hkv, g = blockIdx.y % a.Hkv;
   const int b = a.seq_ids ? a.seq_ids[slot] : slot;
   const int L = max(a.ctx_lens[b], 0);
   const int r0 = a.cu_q[b];
   const int kb = a.cu_q[b + 1] - r0;
+  const int p0 = (L & ~15) + kAppend * (int)blockIdx.x;   // this chunk's first position
+  if (p0 >= L + kb) return;
   const int* pt_row = a.page_table + (size_t)b * a.max_pages;
   DT* kc = reinterpret_cast<DT*>(a.k_cache);
   DT* vc = reinterpret_cast<DT*>(a.v_cache);
   const DT* kn = reinterpret_cast<const DT*>(a.k_new);
   const DT* vn = reinterpret_cast<const DT*>(a.v_new);
-  for (int e = threadIdx.x; e < kb * D; e += blockDim.x) {
-    const int i = e / D, d = e % D;
-    const int pos = L + i;
-    const int page = clampi(pt_row[clampi(pos >> a.log2ps, 0, a.max_pages - 1)], 0, a.num_pages - 1);
+  __shared__ DT s_v[kAppend * LDP];
+  __shared__ int s_pg[kAppend / 16];           // pages are multiples of 16 slots
+  if (threadIdx.x < kAppend / 16)
+    s_pg[threadIdx.x] = clampi(pt_row[clampi((p0 + 16 * (int)threadIdx.x) >> a.log2ps, 0, a.max_pages - 1)],
+                               0, a.num_pages - 1);
+  __syncthreads();
+  for (int e = threadIdx.x; e < kAppend * CPR; e += 256) {
+    const int o = e / CPR, d = e % CPR * EPL;
+    const int pos = p0 + o;
+    if (pos < L || pos >= L + kb) continue;
+    const size_t src = ((size_t)(r0 + pos - L) * a.Hkv + g) * D + d;
+    const size_t page = (size_t)s_pg[o / 16] * a.Hkv + g;
     const int sl = pos & (a.page_size - 1);
-    const size_t src = ((size_t)(r0 + i) * a.Hkv + g) * D + d;
-    kc[((size_t)((page * a.Hkv + g) * (D / 32) + d / 32) * a.page_size + sl) * 32 + (d & 31)] = kn[src];
-    vc[((size_t)(page * a.Hkv + g) * D + d) * a.page_size + sl] = vn[src];
+    DT* kd = kc + ((page * (D / 32) + d / 32) * a.page_size + sl) * 32 + (d & 31);
+    if (a.al16) {
+      *reinterpret_cast<i32x4*>(kd) = ld16<i32x4>(kn + src);
+      const i32x4 vv = ld16<i32x4>(vn + src);
+      const DT* ve = reinterpret_cast<const DT*>(&vv);
+#pragma unroll
+      for (int c = 0; c < EPL; ++c) s_v[o * LDP + d + c] = ve[c];
+    } else {
+      for (int c = 0; c < EPL; ++c) {
+        kd[c] = kn[src + c];
+        s_v[o * LDP + d + c] = vn[src + c];
+      }
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < D * (kAppend / EPL); e += 256) {
+    const int d = e % D, o = e / D * EPL;      // neighbouring lanes: neighbouring channels
+    const int pos = p0 + o;
+    if (pos + EPL <= L || pos >= L + kb) continue;
+    DT* dst = vc + (((size_t)s_pg[o / 16] * a.Hkv + g) * D + d) * a.page_size + (pos & (a.page_size - 1));
+    if (a.al16 && pos >= L && pos + EPL <= L + kb) {
+      i32x4 run;
+      DT* re = reinterpret_cast<DT*>(&run);
+#pragma unroll
+      for (int c = 0; c < EPL; ++c) re[c] = s_v[(o + c) * LDP + d];
+      *reinterpret_cast<i32x4*>(dst) = run;
+    } else {
+      for (int c = 0; c < EPL; ++c)
+        if (pos + c >= L && pos + c < L + kb) dst[c] = s_v[(o + c) * LDP + d];
+    }
   }
 }
 
@@ -1067,6 +1120,176 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // reloads past the end
 }
 
+// ---------------------------------------------------------------------------
+// Long windows (prompts entering the cache, chunked prefill) and short
+// contexts: bf16, D = 128, any page size.
+//
+// With hundreds of window rows per (sequence, KV head) the work is no longer
+// the stream of keys but the two products and the softmax between them, and
+// with short contexts it is the fixed cost of a split; either way a workgroup
+// takes 64 QT query rows and walks all their keys: no split, no partials, no
+// combine, no tables.  Four waves of 16 QT packed rows each share the 32-key
+// units of an LDS ring laid out as below.  QT = 2 at 159 registers and a ring
+// of three units keeps three workgroups on a CU; QT = 3 (221 registers, two
+// workgroups) took 96 us where this takes 82 (eight prompts of 512-1024
+// tokens, teacher heads: 0.45 PFLOP/s; the register kernel took 484), and
+// QT = 4 spills.  What bounds it is the chain within a unit (scores, row
+// maximum, exponentials, second product), of which three waves per SIMD hide
+// a part.  Rows of a wave are neighbours: near the causal edge a wave skips
+// the units past its last row.
+// The grid has (sequence, head) fastest, padded to a multiple of 8, so that
+// all tiles of one (sequence, head) share an XCD's L2 (their keys come from
+// HBM once); the last tiles, which see the most keys, are dealt first.
+// ---------------------------------------------------------------------------
+constexpr int kTileBuf = 3;          // ring depth (units)
+constexpr int kTileBatch = 256;      // units whose page ids are held at a time
+
+template <int PS, int QT>
+__global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) {
+  constexpr int D = 128;
+  constexpr int SUB = PS / 16;             // 16-slot parts per page
+  const int n_sg = a.n_seq * a.Hkv;
+  if ((int)blockIdx.x >= n_sg) return;
+  const int slot = blockIdx.x / a.Hkv, g = blockIdx.x % a.Hkv;
+  const int b = a.seq_ids ? a.seq_ids[slot] : slot;
+  const int L = max(a.ctx_lens[b], 0);
+  const int r0 = a.cu_q[b];
+  const int rows_total = (a.cu_q[b + 1] - r0) * a.G;
+  // tiles from the last one that this window may have (max_q) down
+  const int pr0 = (int)(gridDim.y - 1 - blockIdx.y) * 64 * QT;
+  if (pr0 >= rows_total) return;
+  const int pr_last = min(rows_total, pr0 + 64 * QT) - 1;
+  const int maxblk = (a.max_pages * PS + kBlk - 1) / kBlk;
+  const int n_keys = L + pr_last / a.G + 1;
+  const int nb = min((n_keys + kBlk - 1) / kBlk, maxblk);
+  const int tid = threadIdx.x;
+  const int t = uni(tid / kWave);
+  const int lane = lane_id();
+  const int c16 = lane & 15, j = lane >> 4;
+  const int* pt_row = a.page_table + (size_t)b * a.max_pages;
+  const bf16* kc = reinterpret_cast<const bf16*>(a.k_cache);
+  const bf16* vc = reinterpret_cast<const bf16*>(a.v_cache);
+
+  __shared__ __attribute__((aligned(1024))) char s_ring[kTileBuf * kSkUnit];
+  __shared__ int s_pg[2 * kTileBatch];     // 16-slot parts of the pool: page * SUB + part
+
+  // This wave's rows: tile tt holds wr0 + 16 tt .. wr0 + 16 tt + 15.
+  const int wr0 = pr0 + 16 * QT * t;
+  const bool has_rows = uni(wr0 <= pr_last);
+  RegQT<D, QT> qf;
+  int qlimit[QT];
+#pragma unroll
+  for (int tt = 0; tt < QT; ++tt) {
+    const int pr = wr0 + 16 * tt + c16;
+    const int pc = min(pr, pr_last);
+    qlimit[tt] = L + pc / a.G + 1;
+    const bf16* row = reinterpret_cast<const bf16*>(a.q) +
+                      ((size_t)(r0 + pc / a.G) * a.Hq + g * a.G + pc % a.G) * D + 8 * j;
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) {
+      qf.q[tt][ks] = ld16<bf16x8>(row + 32 * ks);
+      if (pr > pr_last) qf.q[tt][ks] = bf16x8{};
+    }
+  }
+  // units this wave computes: those before its last row's limit; the first
+  // n_full of them reach no row's causal limit and no position past the cache
+  const int w_last = min(wr0 + 16 * QT - 1, pr_last);
+  const int n_mine = has_rows ? uni(min((L + w_last / a.G + 1 + kBlk - 1) / kBlk, nb)) : 0;
+  const int n_full = uni(min((L + pr0 / a.G + 1) / kBlk, nb));   // the same in every wave
+
+  floatx4 acc[QT][D / 16];
+  float m_run[QT], l_run[QT];
+#pragma unroll
+  for (int tt = 0; tt < QT; ++tt) {
+    m_run[tt] = -INFINITY;
+    l_run[tt] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt) acc[tt][dt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  int k_off[2];
+#pragma unroll
+  for (int st = 0; st < 2; ++st) {
+    const int kk = 8 * (c16 >> 2) + 4 * st + (c16 & 3);
+    k_off[st] = 4096 * (kk >> 4) + 16 * kpiece_unit(kk & 15, j);
+  }
+  const int v_off0 = 8192 + 4096 * (j >> 1) + 16 * vpiece_unit(c16, j & 1);
+  const int ksl = lane >> 2;
+  const int k_src = t * (PS * 32) + ksl * 32 + 8 * ((lane & 3) ^ (((ksl >> 1) & 1) | ((ksl >> 2) & 2)));
+  const int vch = lane >> 1;
+  const int v_src = (32 * t + vch) * PS + 8 * ((lane & 1) ^ ((vch >> 2) & 1));
+
+  for (int n0 = 0; n0 < nb; n0 += kTileBatch) {
+    const int n1 = min(n0 + kTileBatch, nb);
+    __syncthreads();                       // the batch before is done with the page ids and the ring
+    for (int e = tid; e < 2 * (n1 - n0); e += 256) {
+      const int p16 = 2 * n0 + e;          // the part's place in the sequence
+      const int page = clampi(pt_row[min(p16 / SUB, a.max_pages - 1)], 0, a.num_pages - 1);
+      s_pg[e] = page * SUB + p16 % SUB;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // only the ring's loads from here on
+    __syncthreads();
+    // Past the batch's end its last unit is loaded again into a free buffer,
+    // so that every wait below has the same count.
+    auto dma = [&](int n) {
+      char* buf = s_ring + (n % kTileBuf) * kSkUnit;
+      const int x = 2 * (min(n, n1 - 1) - n0);
+      const int u0 = uni(s_pg[x]), u1 = uni(s_pg[x + 1]);
+      const size_t b0 = (size_t)(u0 / SUB * a.Hkv + g) * PS * D, b1 = (size_t)(u1 / SUB * a.Hkv + g) * PS * D;
+      const int o0 = u0 % SUB * 16, o1 = u1 % SUB * 16;
+      dma16(kc + b0 + o0 * 32 + k_src, buf + 1024 * t);
+      dma16(vc + b0 + o0 + v_src, buf + 1024 * (8 + t));
+      dma16(kc + b1 + o1 * 32 + k_src, buf + 1024 * (4 + t));
+      dma16(vc + b1 + o1 + v_src, buf + 1024 * (12 + t));
+    };
+    // Unit n has landed for every wave (its own loads by the count, the
+    // others' by the barrier), and every wave is done with unit n - 1, whose
+    // buffer the refill takes (its LDS reads have returned: lgkmcnt).
+    auto next_unit = [&](int n) -> const char* {
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(4 * (kTileBuf - 2)) : "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      dma(n + kTileBuf - 1);
+      return s_ring + (n % kTileBuf) * kSkUnit;
+    };
+#pragma unroll
+    for (int i = 0; i < kTileBuf - 1; ++i) dma(n0 + i);
+    const int f1 = min(n1, n_full);
+    for (int n = n0; n < f1; ++n) {
+      const char* buf = next_unit(n);
+      if (has_rows) {
+        const LdsFrags<false> f{buf, k_off[0], k_off[1], v_off0, 0, 0};
+        attend_block<bf16, D, QT, false>(a, f, qf, qlimit, kBlk * n, acc, m_run, l_run);
+      }
+    }
+    for (int n = max(n0, f1); n < n1; ++n) {
+      const char* buf = next_unit(n);
+      if (n < n_mine) {
+        const LdsFrags<true> f{buf, k_off[0], k_off[1], v_off0, kBlk * n + 8 * j, n_keys};
+        attend_block<bf16, D, QT, true>(a, f, qf, qlimit, kBlk * n, acc, m_run, l_run);
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // reloads past the batch's end
+  }
+
+#pragma unroll
+  for (int tt = 0; tt < QT; ++tt) {
+    float l_tot = l_run[tt] + lane_xor16(l_run[tt]);
+    l_tot += lane_xor32(l_tot);
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    const int pr = wr0 + 16 * tt + c16;
+    if (pr > pr_last) continue;
+    bf16* orow = reinterpret_cast<bf16*>(a.out) +
+                 ((size_t)(r0 + pr / a.G) * a.Hq + g * a.G + pr % a.G) * D;
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt) {
+      bf16x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = static_cast<bf16>(acc[tt][dt][e] * inv);
+      *reinterpret_cast<bf16x4*>(orow + 16 * dt + 4 * j) = v;
+    }
+  }
+}
+
 // Merge the pieces of every item that the stream-K kernel split between
 // workgroups: piece w of item it sits at slot it + w, for the workgroups w
 // whose share of blocks meets the item.
@@ -1184,11 +1407,17 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnParams a) {
   for (int e = 0; e < D / 4; ++e) orow[e] = from_f32<DT>(o[e] * inv);
 }
 
+template <typename DT, int D>
+hipError_t launch_append(const AttnParams& p, hipStream_t st) {
+  const dim3 grid((unsigned)(((long)p.max_q + 15 + kAppend - 1) / kAppend), p.n_seq * p.Hkv);
+  hipLaunchKernelGGL((append_window_kernel<DT, D>), grid, dim3(256), 0, st, p);
+  return hipGetLastError();
+}
+
 template <typename DT, int D, int QT>
 hipError_t launch_t(const AttnParams& p, dim3 grid, dim3 cgrid, hipStream_t st) {
   trace_begin(st);
-  hipLaunchKernelGGL((append_window_kernel<DT, D>), dim3(cgrid.y), dim3(256), 0, st, p);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_append<DT, D>(p, st);
   if (e != hipSuccess) return e;
   trace_mark(st);
   hipLaunchKernelGGL((verify_attn_kernel<DT, D, QT>), grid, dim3(256), 0, st, p);
@@ -1198,6 +1427,21 @@ hipError_t launch_t(const AttnParams& p, dim3 grid, dim3 cgrid, hipStream_t st) 
   hipLaunchKernelGGL((attn_combine_kernel<DT, D>), cgrid, dim3(256), 0, st, p);
   e = hipGetLastError();
   trace_mark(st);
+  return e;
+}
+
+template <int PS, int QT>
+hipError_t launch_tile(const AttnParams& p, hipStream_t st) {
+  trace_begin(st);
+  hipError_t e = launch_append<bf16, 128>(p, st);
+  if (e != hipSuccess) return e;
+  trace_mark(st);
+  const long tiles = ((long)p.max_q * p.G + 64 * QT - 1) / (64 * QT);
+  hipLaunchKernelGGL((verify_attn_tile_kernel<PS, QT>),
+                     dim3((p.n_seq * p.Hkv + 7) / 8 * 8, (unsigned)tiles), dim3(256), 0, st, p);
+  e = hipGetLastError();
+  trace_mark(st);
+  trace_mark(st);   // no combine: an empty interval
   return e;
 }
 
@@ -1280,6 +1524,24 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
   const long share = std::max((n_it * (4 * maxblk + c4) * wmax + wden - 1) / wden, (c4 + 3) / 4 + 1) + 2;
   pl.sk = D == 128 && page_size == 16 && n_it * (4 * maxblk + c4) < (1L << 31) &&
           2 * (n_it + 1) + 4L * n_seq + 3 * share + pl.sk_qt * n_it <= kSkMeta;
+  // Tiles without a split (verify_attn_tile_kernel), or shares of all items
+  // (stream-K).  A tile walks its keys at 0.75 us per 32-key block however
+  // many tiles there are, up to about one per compute unit; stream-K spreads
+  // every item over the chip but pays its tables, the partials and the
+  // combine (9 us at 64-row items, 14 us at 128-row ones), and every item of
+  // a window appends it again (0.03 us per window row).  By the host's bounds
+  // of keys and rows, measured on both sides of the line (us, tile / stream-K):
+  //   64 teacher windows of 8 rows, contexts to 300 / 1000 / 8192: 16 / 24,
+  //   29 / 37, 190 / 131; 4 of them, contexts to 1000: 25 / 20;
+  //   16 windows of 32 rows, contexts to 1000: 38 / 35; one prompt of 1024
+  //   teacher tokens: 41 / 92; 4 windows of 256 rows, contexts to 4096: 119 / 109.
+  // More items than the stream-K tables hold, with more than 64 rows each,
+  // fill the chip as tiles at any length (eight prompts of 512-1024 tokens:
+  // register kernel 484 us, tiles 82 us).
+  const double fixed = (pl.sk_qt == 2 ? 14 : 9) + 0.03 * max_q;
+  if (D == 128 && (0.75 * maxblk <= fixed + 0.002 * std::min(n_it, 256L) * maxblk ||
+                   (!pl.sk && n_it >= kSkGrid && rows > kRows)))
+    pl.tile = pl.sk_qt;
   if (pl.sk) {
     const size_t sk_slots = (size_t)n_it + kSkGrid;
     const size_t sk_rows = 64 * (size_t)pl.sk_qt;
@@ -1360,9 +1622,21 @@ hipError_t launch_verify_attn(const AttnLaunch& L, const AttnPlan& pl, hipStream
   p.max_chunks = pl.max_chunks;
   p.n_qg = pl.n_qg;
   p.n_seq = L.n_seq;
+  p.max_q = L.max_q;
+  const uintptr_t bases = reinterpret_cast<uintptr_t>(L.q) | reinterpret_cast<uintptr_t>(L.k_new) |
+                          reinterpret_cast<uintptr_t>(L.v_new) | reinterpret_cast<uintptr_t>(L.k_cache) |
+                          reinterpret_cast<uintptr_t>(L.v_cache);
+  p.al16 = (bases & 15) == 0;
   p.scale_log2 = L.scale * 1.4426950408889634f;
   dim3 grid((L.n_seq * L.Hkv + 7) / 8 * 8, pl.n_qg, pl.max_chunks);
   dim3 cgrid(pl.n_qg, L.n_seq * L.Hkv);
+  if (pl.tile && L.dtype_bf16 && L.D == 128 && p.al16) {
+    switch (L.page_size) {
+      case 16: return pl.tile == 1 ? launch_tile<16, 1>(p, st) : launch_tile<16, 2>(p, st);
+      case 32: return pl.tile == 1 ? launch_tile<32, 1>(p, st) : launch_tile<32, 2>(p, st);
+      default: return pl.tile == 1 ? launch_tile<64, 1>(p, st) : launch_tile<64, 2>(p, st);
+    }
+  }
   if (pl.sk && L.dtype_bf16 && L.D == 128 && L.page_size == 16) {
     p.part_lse = reinterpret_cast<float*>(reinterpret_cast<char*>(L.workspace) + pl.sk_o_bytes);
     p.sk_start = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(L.workspace) + pl.sk_o_bytes + pl.sk_lse_bytes);

@@ -1,0 +1,97 @@
+"""GPU parity of verify_attn_paged on its unsplit tiles (long windows and short
+contexts) and of the window append, against the fp64 oracle, and of the
+stream-K split on batches of the same lengths when the page table is wide."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2609_36546_amd import inputs, ops
+from tests import parity
+from tests.workload import to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(Hq, Hkv, ks, lo, hi, ps, seed, B=4, D=128, dtype="bf16"):
+    shape = inputs.ModelShape("heads", Hq=Hq, Hkv=Hkv, D=D, hidden=64, vocab=512)
+    cfg = inputs.scaled(inputs.WORKLOADS["teacher-bf16"], B=B, ctx_lo=lo, ctx_hi=hi, k_choices=ks,
+                        page_size=ps, models=(shape,), dtype=dtype)
+    print(f"[tiles] heads {Hq}/{Hkv} D={D} B={B} ctx=[{lo},{hi}] k={ks} ps={ps} seed={seed}", flush=True)
+    return inputs.make_batch(cfg, seed=seed, device="cuda")
+
+
+def _check(b, **kw):
+    mdl = b.models[0]
+    out, kc, vc = parity.run_gpu_attention(mdl, b, seq_ids=mdl.seq_ids, **kw)
+    ref, rkc, rvc = parity.oracle_attention(mdl, b, to_np(mdl.seq_ids).astype(np.int64), mdl.shape.D)
+    parity.check_attention_rows(out, ref, to_np(mdl.rows).astype(np.int64), mdl.q.dtype)
+    np.testing.assert_array_equal(to_np(kc), rkc.astype(np.float32))
+    np.testing.assert_array_equal(to_np(vc), rvc.astype(np.float32))
+
+
+def _wide(mdl, pages):
+    """The page table with more columns than any sequence needs (poison pages)."""
+    pt = mdl.page_table
+    pad = torch.full((pt.shape[0], pages), mdl.poison_page, dtype=pt.dtype, device=pt.device)
+    return torch.cat([pt, pad], 1).contiguous()
+
+
+@pytest.mark.parametrize("ps", [16, 32, 64])
+@pytest.mark.parametrize("Hq,Hkv,ks,lo,hi", [
+    (32, 4, (1, 37, 130), 0, 0),        # prompts: up to nine 128-row tiles, the last partly filled
+    (16, 8, (1, 5, 31, 0), 0, 90),      # one 64-row tile, empty windows among them
+    (16, 8, (33, 64), 17, 200),         # two query heads per KV head: exactly one 128-row tile, and one row over 64
+    (4, 4, (1, 16, 65), 30, 33),        # one query head per KV head, contexts around one key block
+])
+def test_tiles(Hq, Hkv, ks, lo, hi, ps):
+    _check(_batch(Hq, Hkv, ks, lo, hi, ps, seed=50 + ps))
+
+
+def test_tiles_over_two_batches_of_page_ids():
+    """More than 256 key blocks per tile: the page ids are read in two batches
+    (a generous max_q makes the planner take the tiles)."""
+    _check(_batch(8, 4, (1, 5), 8150, 8300, 16, seed=61, B=3), max_q=8000)
+
+
+@pytest.mark.parametrize("D,dtype,ps", [(64, "bf16", 32), (64, "f32", 16)])
+def test_append_of_long_windows(D, dtype, ps):
+    """Windows over several 64-position chunks of the append, starting and
+    ending inside a run of slots."""
+    _check(_batch(4, 2, (3, 64, 131), 5, 150, ps, seed=62, D=D, dtype=dtype))
+
+
+def test_append_of_arrays_off_a_16_byte_boundary():
+    """Caches that start 8 bytes off a 16-byte boundary take the register
+    kernel and the append's element-wise path."""
+    b = _batch(8, 4, (1, 7, 40), 5, 150, 32, seed=63)
+    mdl = b.models[0]
+
+    def moved(x):
+        buf = torch.empty(x.numel() + 4, dtype=x.dtype, device=x.device)
+        y = buf[4:].view(x.shape)
+        y.copy_(x)
+        assert y.data_ptr() % 16 == 8
+        return y
+
+    kc, vc = moved(mdl.k_pool), moved(mdl.v_pool)
+    dev = mdl.q.device
+    out = ops.verify_attn_paged(mdl.q, mdl.k_new, mdl.v_new, kc, vc, mdl.page_table,
+                                torch.from_numpy(b.ctx_lens).to(dev), torch.from_numpy(b.cu_q).to(dev), max_q=40)
+    ref, rkc, rvc = parity.oracle_attention(mdl, b, to_np(mdl.seq_ids).astype(np.int64), 128)
+    parity.check_attention_rows(out, ref, to_np(mdl.rows).astype(np.int64), mdl.q.dtype)
+    np.testing.assert_array_equal(to_np(kc), rkc.astype(np.float32))
+    np.testing.assert_array_equal(to_np(vc), rvc.astype(np.float32))
+
+
+@pytest.mark.parametrize("Hq,Hkv,ks,lo,hi,B", [
+    (32, 4, (0, 1, 8, 16), 0, 300, 12),   # items without rows between others
+    (32, 4, (0, 4, 16), 0, 40, 60),       # fewer key blocks than workgroups
+    (32, 2, (16, 5, 0), 0, 700, 5),       # two 128-row items over the same keys
+    (16, 8, (1, 8), 480, 540, 64),        # shares around eight blocks
+    (16, 8, (1,), 0, 60, 1),              # a single short sequence
+])
+def test_stream_k_with_a_wide_page_table(Hq, Hkv, ks, lo, hi, B):
+    """Short contexts under a page table sized for long ones: the planner goes
+    by the table's width, so these batches take the stream-K split."""
+    b = _batch(Hq, Hkv, ks, lo, hi, 16, seed=64, B=B)
+    _check(b, page_table=_wide(b.models[0], 2048))
