@@ -40,8 +40,7 @@
 // log-sum-exp form, unless the sequence fits in one chunk (then the
 // workgroup writes the output itself).
 //
-// bf16 D = 128 heads in 16-token pages (every bf16 workload), when the
-// kernel's LDS tables fit, take a second kernel, verify_attn_sk_kernel below:
+// bf16 D = 128 heads (every bf16 workload), when the kernel's LDS tables fit, take a second kernel, verify_attn_sk_kernel below:
 // persistent workgroups whose waves own one or two 16-row tiles (items of 64
 // or 128 rows of one (sequence, KV head)), keys and values streamed through
 // an LDS ring with direct-to-LDS loads, and the key blocks of all items split
@@ -590,8 +589,7 @@ __global__ __launch_bounds__(256) void verify_attn_kernel(AttnParams a) {
 }
 
 // ---------------------------------------------------------------------------
-// Persistent stream-K variant for full 64-row groups (bf16, D = 128, 16-token
-// pages).
+// Persistent stream-K variant (bf16, D = 128).
 //
 // The register kernel above holds all four 16-row tiles of a group in every
 // wave, so one wave fits per SIMD; and like any kernel of one workgroup per
@@ -616,15 +614,21 @@ __global__ __launch_bounds__(256) void verify_attn_kernel(AttnParams a) {
 // leaves one partial per piece, at slot item + workgroup, and the combine
 // kernel merges them.
 //
-// LDS image of a key/value unit: [K page 0][K page 1][V page 0][V page 1],
-// each a 4 KB page of the pool in its own layout (keys [D/32][slot][32],
-// values [D][slot]); of a query unit: 64 rows of 256 bytes.  Within every
-// 1 KB piece the 16-byte units are permuted so that the fragment reads of
-// eight consecutive lanes hit eight distinct bank groups: unit (slot, q) of a
-// key piece sits at 4 slot + (q ^ f(slot)), unit (channel, half) of a value
-// piece at 2 channel + (half ^ bit 2 of the channel), unit u of query row r
-// at u ^ (r % 8).  A direct-to-LDS load writes lane l's 16 bytes to unit l,
-// so the loading lane fetches the global unit that belongs there.
+// LDS image of a key/value unit (32 keys, two 16-slot parts of pages):
+// [K part 0][K part 1][V], 4 KB, 4 KB, 8 KB.  A key part is four 1 KB pieces,
+// one per 32-channel slice, of 16 slots.  With 16-slot pages the values are
+// the two pages in their own layout, [part][channel][16 slots]; with larger
+// pages both parts lie in one page and a channel's 32 keys are together,
+// [channel][32 slots], so that a load instruction reads 64-byte runs of the
+// page's channel rows.  A query unit is 64 rows of 256 bytes.  Within every
+// 1 KB piece the 16-byte units are permuted so that the lanes a 16-byte LDS
+// read serves at once (lanes 0-3, 12-15, 20-27; 4-11, 16-19, 28-31; the same
+// in the upper half) hit distinct bank groups: unit (slot, q) of a key piece
+// sits at 4 slot + (q ^ f(slot)), unit (channel, half) of a 16-slot value
+// piece at 2 channel + (half ^ bit 2 of the channel), unit (channel, q) of a
+// 32-slot one at 4 channel + (q ^ h(channel)), unit u of query row r at
+// u ^ (r % 8).  A direct-to-LDS load writes lane l's 16 bytes to unit l, so
+// the loading lane fetches the global unit that belongs there.
 // ---------------------------------------------------------------------------
 constexpr int kSkBuf = 3;              // ring depth (units)
 constexpr int kSkUnit = 16384;         // bytes per unit
@@ -635,19 +639,71 @@ __device__ __forceinline__ int kpiece_unit(int slot, int q) {
   return 4 * slot + (q ^ (((slot >> 1) & 1) | ((slot >> 2) & 2)));
 }
 __device__ __forceinline__ int vpiece_unit(int ch, int h) { return 2 * ch + (h ^ ((ch >> 2) & 1)); }
+__device__ __forceinline__ int vpiece32_unit(int ch, int q) {
+  const int c4 = (ch >> 2) & 3;
+  return 4 * ch + (q ^ (((c4 << 1) ^ (3 * (c4 >> 1))) & 3));
+}
+
+// Byte offset in a key/value unit of the lane's value fragment of channels
+// 0-15 (channel c16, keys 8 j .. 8 j + 7); the next 16 channels are
+// kSkVStep<PS> bytes on.
+template <int PS> constexpr int kSkVStep = PS == 16 ? 512 : 1024;
+template <int PS> __device__ __forceinline__ int v_frag_off(int c16, int j) {
+  return PS == 16 ? 8192 + 4096 * (j >> 1) + 16 * vpiece_unit(c16, j & 1) : 8192 + 16 * vpiece32_unit(c16, j);
+}
+
+// The sources of wave t's quarter of every key/value unit: element offsets
+// within a page's (KV head) keys and values for this lane.  Keys: slice t of
+// both parts.  Values, 16-slot pages: channels 32 t .. 32 t + 31 of both
+// parts; larger pages: channels 32 t .. 32 t + 15, then the next 16.
+template <int PS> struct SkSrc {
+  int k, v;
+  __device__ __forceinline__ explicit SkSrc(int t) {
+    const int lane = lane_id();
+    const int sl = lane >> 2;
+    k = t * (PS * 32) + sl * 32 + 8 * ((lane & 3) ^ (kpiece_unit(sl, 0) & 3));
+    if constexpr (PS == 16) {
+      const int ch = lane >> 1;
+      v = (32 * t + ch) * PS + 8 * ((lane & 1) ^ ((ch >> 2) & 1));
+    } else {
+      const int ch = lane >> 2;
+      v = (32 * t + ch) * PS + 8 * ((lane & 3) ^ (vpiece32_unit(ch, 0) & 3));
+    }
+  }
+  // Issues the quarter of the unit whose parts are u0 and u1 (page * PS / 16
+  // + part) of KV head g.
+  __device__ __forceinline__ void load(const bf16* kc, const bf16* vc, int u0, int u1, int Hkv, int g,
+                                       char* buf, int t) const {
+    constexpr int D = 128, SUB = PS / 16;
+    const size_t b0 = (size_t)(u0 / SUB * Hkv + g) * PS * D;
+    const int o0 = u0 % SUB * 16;
+    if constexpr (PS == 16) {
+      const size_t b1 = (size_t)(u1 * Hkv + g) * PS * D;
+      dma16(kc + b0 + k, buf + 1024 * t);
+      dma16(vc + b0 + v, buf + 1024 * (8 + t));
+      dma16(kc + b1 + k, buf + 1024 * (4 + t));
+      dma16(vc + b1 + v, buf + 1024 * (12 + t));
+    } else {
+      dma16(kc + b0 + o0 * 32 + k, buf + 1024 * t);
+      dma16(vc + b0 + o0 + v, buf + 1024 * (8 + 2 * t));
+      dma16(kc + b0 + (o0 + 16) * 32 + k, buf + 1024 * (4 + t));
+      dma16(vc + b0 + o0 + 16 * PS + v, buf + 1024 * (9 + 2 * t));
+    }
+  }
+};
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 // MFMA operands read from a key/value unit in LDS where they are used, so
 // that no full register copy of the block is live.  TAIL: value lanes of keys
 // at or past n_keys are zeroed (their pages are clamped stand-ins).
-template <bool TAIL> struct LdsFrags {
+template <bool TAIL, int VSTEP> struct LdsFrags {
   const char* buf;
   int k_off0, k_off1, v_off0, vpos, n_keys;
   __device__ __forceinline__ bf16x8 kf(int st, int ks) const {
     return *reinterpret_cast<const bf16x8*>(buf + (st ? k_off1 : k_off0) + 1024 * ks);
   }
   __device__ __forceinline__ bf16x8 vf(int dt) const {
-    bf16x8 v = *reinterpret_cast<const bf16x8*>(buf + v_off0 + 512 * dt);
+    bf16x8 v = *reinterpret_cast<const bf16x8*>(buf + v_off0 + VSTEP * dt);
     if constexpr (TAIL) {
 #pragma unroll
       for (int e = 0; e < 8; ++e)
@@ -730,11 +786,11 @@ __device__ __forceinline__ SkItem sk_item(const AttnParams& a, const int* s_seq,
   return m;
 }
 
-template <int QT>
+template <int PS, int QT>
 __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
   static_assert(QT == 1 || QT == 2, "tiles per wave");
   constexpr int D = 128;
-  constexpr int PS = 16;
+  constexpr int SUB = PS / 16;         // 16-slot parts per page
   constexpr int kRowsI = 64 * QT;      // rows per item: QT query units of 64 rows
   const int tid = threadIdx.x;
   const int t = uni(tid / kWave);      // row tile (wave-uniform)
@@ -750,7 +806,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
   int* s_start = s_meta;                    // [n_it + 1] first block of each item
   int* s_ne = s_start + n_it + 1;           // [n_it + 1] non-empty items before each item
   int* s_seq = s_ne + n_it + 1;             // [n_seq][4]: b, L, r0, rows
-  int* s_pg = s_seq + 4 * a.n_seq;          // [2 per block]: page ids of this workgroup's blocks
+  int* s_pg = s_seq + 4 * a.n_seq;          // [2 per block]: 16-slot parts of the pool, page * SUB + part
 
   // Sequence data, then every item's block count, and the exclusive scans of
   // the block counts and of the non-empty flags.
@@ -863,10 +919,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
   int* s_uq = s_pg + 2 * (hi - lo);          // [n_units] the workgroup's units, in order
   // Lane-fixed parts of this wave's loads: key slice t and value channels
   // 32t .. 32t+31 of each page; query rows 16t .. 16t+15, four per load.
-  const int ksl = lane >> 2;
-  const int k_src = t * (PS * 32) + ksl * 32 + 8 * ((lane & 3) ^ (((ksl >> 1) & 1) | ((ksl >> 2) & 2)));
-  const int vch = lane >> 1;
-  const int v_src = (32 * t + vch) * PS + 8 * ((lane & 1) ^ ((vch >> 2) & 1));
+  const SkSrc<PS> src(t);
   const bf16* kc = reinterpret_cast<const bf16*>(a.k_cache);
   const bf16* vc = reinterpret_cast<const bf16*>(a.v_cache);
   const bf16* qp = reinterpret_cast<const bf16*>(a.q);
@@ -890,12 +943,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
         dma16(row + 8 * ((lane & 15) ^ (r & 7)), buf + 1024 * (4 * t + u));
       }
     } else {
-      const size_t b0 = (size_t)(d_pg0 * a.Hkv + d_g) * PS * D;
-      const size_t b1 = (size_t)(d_pg1 * a.Hkv + d_g) * PS * D;
-      dma16(kc + b0 + k_src, buf + 1024 * t);
-      dma16(vc + b0 + v_src, buf + 1024 * (8 + t));
-      dma16(kc + b1 + k_src, buf + 1024 * (4 + t));
-      dma16(vc + b1 + v_src, buf + 1024 * (12 + t));
+      src.load(kc, vc, d_pg0, d_pg1, a.Hkv, d_g, buf, t);
     }
   };
   auto dma_next = [&](int m) {
@@ -921,7 +969,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
   // thread's first block stay in registers until the window append below has
   // issued its own loads, so that both sets of loads are in flight together;
   // those of further blocks (shares above 256 blocks) are written at once.
-  int pg_x = -1, pg_a = 0, pg_b = 0;
+  int pg_x = -1, pg_a = 0, pg_b = 0, pg_pl = 0;
   for (int x = lo + tid; x < hi; x += 256) {
     const int i = item_of(x, i_first, i_last);
     const int u = (x - lo) + QT * (s_ne[i + 1] - s_ne[i_first]);
@@ -931,15 +979,16 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
       for (int h = 0; h < QT; ++h) s_uq[u - QT + h] = 4 * i + 2 * h + 1;
     const SkItem m = sk_item(a, s_seq, i, maxblk);
     const int* pt_row = a.page_table + (size_t)m.b * a.max_pages;
-    const int pl = 2 * (x - s_start[i]);
-    const int ga = pt_row[min(pl, a.max_pages - 1)], gb = pt_row[min(pl + 1, a.max_pages - 1)];
+    const int pl = 2 * (x - s_start[i]);     // the block's first 16-slot part in the sequence
+    const int ga = pt_row[min(pl / SUB, a.max_pages - 1)], gb = pt_row[min((pl + 1) / SUB, a.max_pages - 1)];
     if (pg_x < 0) {
       pg_x = x;
       pg_a = ga;
       pg_b = gb;
+      pg_pl = pl;
     } else {
-      s_pg[2 * (x - lo)] = clampi(ga, 0, a.num_pages - 1);
-      s_pg[2 * (x - lo) + 1] = clampi(gb, 0, a.num_pages - 1);
+      s_pg[2 * (x - lo)] = clampi(ga, 0, a.num_pages - 1) * SUB + pl % SUB;
+      s_pg[2 * (x - lo) + 1] = clampi(gb, 0, a.num_pages - 1) * SUB + (pl + 1) % SUB;
     }
   }
 
@@ -962,7 +1011,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
       const int* pt_row = a.page_table + (size_t)m.b * a.max_pages;
       for (int e = tid; e < (p_hi - p_lo) * (D / 8); e += 256) {
         const int pos = p_lo + e / (D / 8), d0 = 8 * (e % (D / 8));
-        const int page = clampi(pt_row[clampi(pos >> 4, 0, a.max_pages - 1)], 0, a.num_pages - 1);
+        const int page = clampi(pt_row[clampi(pos / PS, 0, a.max_pages - 1)], 0, a.num_pages - 1);
         const int sl = pos & (PS - 1);
         const size_t src = ((size_t)(m.r0 + pos - m.L) * a.Hkv + m.g) * D + d0;
         const bf16x8 kv = *reinterpret_cast<const bf16x8*>(kn + src);
@@ -975,8 +1024,8 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
     }
   }
   if (pg_x >= 0) {
-    s_pg[2 * (pg_x - lo)] = clampi(pg_a, 0, a.num_pages - 1);
-    s_pg[2 * (pg_x - lo) + 1] = clampi(pg_b, 0, a.num_pages - 1);
+    s_pg[2 * (pg_x - lo)] = clampi(pg_a, 0, a.num_pages - 1) * SUB + pg_pl % SUB;
+    s_pg[2 * (pg_x - lo) + 1] = clampi(pg_b, 0, a.num_pages - 1) * SUB + (pg_pl + 1) % SUB;
   }
 
   // The window's stores and the page-table reads are done and the tables are
@@ -986,16 +1035,14 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
   dma_next(0);
   for (int m = 1; m < kSkBuf - 1; ++m) dma_unit(m);
 
-  // Per-lane LDS offsets of the MFMA operands within a unit.  Channel
-  // 16 dt + c16 lies in value piece dt / 2 at unit 2 (16 (dt % 2) + c16) + h',
-  // and h' does not depend on dt, so the value offsets step by 512 bytes.
+  // Per-lane LDS offsets of the MFMA operands within a unit.
   int k_off[2];
 #pragma unroll
   for (int st = 0; st < 2; ++st) {
     const int kk = 8 * (c16 >> 2) + 4 * st + (c16 & 3);
     k_off[st] = 4096 * (kk >> 4) + 16 * kpiece_unit(kk & 15, j);
   }
-  const int v_off0 = 8192 + 4096 * (j >> 1) + 16 * vpiece_unit(c16, j & 1);
+  const int v_off0 = v_frag_off<PS>(c16, j);
 
   // Compute side.  The units come as items: QT query units, then the item's
   // key/value units up to the one that ends its piece.  Tile tt of this wave
@@ -1068,7 +1115,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
       if (t0 + kBlk > main_end) break;
       const char* buf = next_unit(rec);
       if (has_rows[0]) {
-        const LdsFrags<false> f{buf, k_off[0], k_off[1], v_off0, 0, 0};
+        const LdsFrags<false, kSkVStep<PS>> f{buf, k_off[0], k_off[1], v_off0, 0, 0};
         attend_block<bf16, D, QT, false>(a, f, qf, qlimit, t0, acc, m_run, l_run);
       }
       if (rec & 2) { ended = true; break; }
@@ -1077,7 +1124,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
       const char* buf = next_unit(rec);
       const int t0 = kBlk * ((rec >> 2) - x0);
       if (has_rows[0]) {
-        const LdsFrags<true> f{buf, k_off[0], k_off[1], v_off0, t0 + 8 * j, it.n_keys};
+        const LdsFrags<true, kSkVStep<PS>> f{buf, k_off[0], k_off[1], v_off0, t0 + 8 * j, it.n_keys};
         attend_block<bf16, D, QT, true>(a, f, qf, qlimit, t0, acc, m_run, l_run);
       }
       ended = rec & 2;
@@ -1212,11 +1259,8 @@ __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) 
     const int kk = 8 * (c16 >> 2) + 4 * st + (c16 & 3);
     k_off[st] = 4096 * (kk >> 4) + 16 * kpiece_unit(kk & 15, j);
   }
-  const int v_off0 = 8192 + 4096 * (j >> 1) + 16 * vpiece_unit(c16, j & 1);
-  const int ksl = lane >> 2;
-  const int k_src = t * (PS * 32) + ksl * 32 + 8 * ((lane & 3) ^ (((ksl >> 1) & 1) | ((ksl >> 2) & 2)));
-  const int vch = lane >> 1;
-  const int v_src = (32 * t + vch) * PS + 8 * ((lane & 1) ^ ((vch >> 2) & 1));
+  const int v_off0 = v_frag_off<PS>(c16, j);
+  const SkSrc<PS> src(t);
 
   for (int n0 = 0; n0 < nb; n0 += kTileBatch) {
     const int n1 = min(n0 + kTileBatch, nb);
@@ -1233,13 +1277,7 @@ __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) 
     auto dma = [&](int n) {
       char* buf = s_ring + (n % kTileBuf) * kSkUnit;
       const int x = 2 * (min(n, n1 - 1) - n0);
-      const int u0 = uni(s_pg[x]), u1 = uni(s_pg[x + 1]);
-      const size_t b0 = (size_t)(u0 / SUB * a.Hkv + g) * PS * D, b1 = (size_t)(u1 / SUB * a.Hkv + g) * PS * D;
-      const int o0 = u0 % SUB * 16, o1 = u1 % SUB * 16;
-      dma16(kc + b0 + o0 * 32 + k_src, buf + 1024 * t);
-      dma16(vc + b0 + o0 + v_src, buf + 1024 * (8 + t));
-      dma16(kc + b1 + o1 * 32 + k_src, buf + 1024 * (4 + t));
-      dma16(vc + b1 + o1 + v_src, buf + 1024 * (12 + t));
+      src.load(kc, vc, uni(s_pg[x]), uni(s_pg[x + 1]), a.Hkv, g, buf, t);
     };
     // Unit n has landed for every wave (its own loads by the count, the
     // others' by the barrier), and every wave is done with unit n - 1, whose
@@ -1257,14 +1295,14 @@ __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) 
     for (int n = n0; n < f1; ++n) {
       const char* buf = next_unit(n);
       if (has_rows) {
-        const LdsFrags<false> f{buf, k_off[0], k_off[1], v_off0, 0, 0};
+        const LdsFrags<false, kSkVStep<PS>> f{buf, k_off[0], k_off[1], v_off0, 0, 0};
         attend_block<bf16, D, QT, false>(a, f, qf, qlimit, kBlk * n, acc, m_run, l_run);
       }
     }
     for (int n = max(n0, f1); n < n1; ++n) {
       const char* buf = next_unit(n);
       if (n < n_mine) {
-        const LdsFrags<true> f{buf, k_off[0], k_off[1], v_off0, kBlk * n + 8 * j, n_keys};
+        const LdsFrags<true, kSkVStep<PS>> f{buf, k_off[0], k_off[1], v_off0, kBlk * n + 8 * j, n_keys};
         attend_block<bf16, D, QT, true>(a, f, qf, qlimit, kBlk * n, acc, m_run, l_run);
       }
     }
@@ -1445,6 +1483,7 @@ hipError_t launch_tile(const AttnParams& p, hipStream_t st) {
   return e;
 }
 
+template <int PS>
 hipError_t launch_sk(const AttnParams& p, dim3 cgrid, hipStream_t st) {
   // The window append happens inside the attention kernel (an empty
   // interval in the trace where the other path has its append kernel).
@@ -1452,9 +1491,9 @@ hipError_t launch_sk(const AttnParams& p, dim3 cgrid, hipStream_t st) {
   trace_mark(st);
   hipError_t e;
   if (p.item_rows == 128)
-    hipLaunchKernelGGL(verify_attn_sk_kernel<2>, dim3(p.sk_grid), dim3(256), 0, st, p);
+    hipLaunchKernelGGL((verify_attn_sk_kernel<PS, 2>), dim3(p.sk_grid), dim3(256), 0, st, p);
   else
-    hipLaunchKernelGGL(verify_attn_sk_kernel<1>, dim3(p.sk_grid), dim3(256), 0, st, p);
+    hipLaunchKernelGGL((verify_attn_sk_kernel<PS, 1>), dim3(p.sk_grid), dim3(256), 0, st, p);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   trace_mark(st);
@@ -1503,7 +1542,7 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
   pl.part_o_bytes = slots * kRows * D * sizeof(float);
   pl.part_lse_bytes = slots * kRows * sizeof(float);
   pl.workspace_bytes = pl.part_o_bytes + pl.part_lse_bytes + 256;
-  // D = 128 heads in 16-slot pages take the persistent stream-K kernel (bf16;
+  // D = 128 heads take the persistent stream-K kernel (bf16;
   // the launch checks the type) when its LDS tables fit: item starts and
   // non-empty counts, sequence data, and per workgroup two page ids per
   // block and one record per unit (its units add sk_qt per item).
@@ -1520,9 +1559,21 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
   const long c4 = sk_item_cost(pl.sk_qt);
   const long wmax = std::max(std::max(kSkSpan[0], kSkSpan[1]), std::max(kSkSpan[2], kSkSpan[3]));
   const long wmin = std::min(std::min(kSkSpan[0], kSkSpan[1]), std::min(kSkSpan[2], kSkSpan[3]));
-  const long wden = 4L * kSkGrid * wmin;
+  // Partials: one per item and workgroup boundary.  16-slot pages size the
+  // workspace for the full grid; with other page sizes the workspace stays
+  // what the register kernel needs, and the grid shrinks to what it holds
+  // (below 128 workgroups the register kernel is taken).
+  const size_t sk_rows = 64 * (size_t)pl.sk_qt;
+  const size_t tables = 2 * (size_t)(n_it + 1) * sizeof(int32_t) + 256;
+  pl.sk_grid = kSkGrid;
+  if (page_size != 16) {
+    const long held = (long)((pl.workspace_bytes - std::min(pl.workspace_bytes, tables)) /
+                             (sk_rows * (D + 1) * sizeof(float))) - n_it;
+    pl.sk_grid = (int)std::max(0L, std::min((long)kSkGrid, held & ~1L));
+  }
+  const long wden = 4L * std::max(pl.sk_grid, 1) * wmin;
   const long share = std::max((n_it * (4 * maxblk + c4) * wmax + wden - 1) / wden, (c4 + 3) / 4 + 1) + 2;
-  pl.sk = D == 128 && page_size == 16 && n_it * (4 * maxblk + c4) < (1L << 31) &&
+  pl.sk = D == 128 && pl.sk_grid >= 128 && n_it * (4 * maxblk + c4) < (1L << 31) &&
           2 * (n_it + 1) + 4L * n_seq + 3 * share + pl.sk_qt * n_it <= kSkMeta;
   // Tiles without a split (verify_attn_tile_kernel), or shares of all items
   // (stream-K).  A tile walks its keys at 0.75 us per 32-key block however
@@ -1543,11 +1594,14 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
                    (!pl.sk && n_it >= kSkGrid && rows > kRows)))
     pl.tile = pl.sk_qt;
   if (pl.sk) {
-    const size_t sk_slots = (size_t)n_it + kSkGrid;
-    const size_t sk_rows = 64 * (size_t)pl.sk_qt;
-    pl.sk_o_bytes = std::max(pl.part_o_bytes, sk_slots * sk_rows * D * sizeof(float));
-    pl.sk_lse_bytes = std::max(pl.part_lse_bytes, sk_slots * sk_rows * sizeof(float));
-    pl.workspace_bytes = pl.sk_o_bytes + pl.sk_lse_bytes + 2 * (n_it + 1) * sizeof(int32_t) + 256;
+    const size_t sk_slots = (size_t)n_it + pl.sk_grid;
+    pl.sk_o_bytes = sk_slots * sk_rows * D * sizeof(float);
+    pl.sk_lse_bytes = sk_slots * sk_rows * sizeof(float);
+    if (page_size == 16) {
+      pl.sk_o_bytes = std::max(pl.part_o_bytes, pl.sk_o_bytes);
+      pl.sk_lse_bytes = std::max(pl.part_lse_bytes, pl.sk_lse_bytes);
+      pl.workspace_bytes = pl.sk_o_bytes + pl.sk_lse_bytes + tables;
+    }
   }
   return pl;
 }
@@ -1637,15 +1691,20 @@ hipError_t launch_verify_attn(const AttnLaunch& L, const AttnPlan& pl, hipStream
       default: return pl.tile == 1 ? launch_tile<64, 1>(p, st) : launch_tile<64, 2>(p, st);
     }
   }
-  if (pl.sk && L.dtype_bf16 && L.D == 128 && L.page_size == 16) {
+  if (pl.sk && L.dtype_bf16 && L.D == 128 && (L.page_size == 16 || p.al16)) {
     p.part_lse = reinterpret_cast<float*>(reinterpret_cast<char*>(L.workspace) + pl.sk_o_bytes);
     p.sk_start = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(L.workspace) + pl.sk_o_bytes + pl.sk_lse_bytes);
     p.sk_ne = p.sk_start + ((size_t)L.n_seq * L.Hkv * pl.sk_n_qg + 1);
-    p.sk_grid = kSkGrid;
+    p.sk_grid = pl.sk_grid;
     p.sk_first = device_cus();
     p.n_qg = pl.sk_n_qg;
     p.item_rows = 64 * pl.sk_qt;
-    return launch_sk(p, dim3(pl.sk_n_qg, L.n_seq * L.Hkv), st);
+    const dim3 sgrid(pl.sk_n_qg, L.n_seq * L.Hkv);
+    switch (L.page_size) {
+      case 16: return launch_sk<16>(p, sgrid, st);
+      case 32: return launch_sk<32>(p, sgrid, st);
+      default: return launch_sk<64>(p, sgrid, st);
+    }
   }
   if (L.dtype_bf16) {
     return L.D == 64 ? launch_d<bf16, 64>(p, pl.qt, grid, cgrid, st)

@@ -83,15 +83,17 @@ def test_append_of_arrays_off_a_16_byte_boundary():
     np.testing.assert_array_equal(to_np(vc), rvc.astype(np.float32))
 
 
-@pytest.mark.parametrize("Hq,Hkv,ks,lo,hi,B", [
-    (32, 4, (0, 1, 8, 16), 0, 300, 12),   # items without rows between others
-    (32, 4, (0, 4, 16), 0, 40, 60),       # fewer key blocks than workgroups
-    (32, 2, (16, 5, 0), 0, 700, 5),       # two 128-row items over the same keys
-    (16, 8, (1, 8), 480, 540, 64),        # shares around eight blocks
-    (16, 8, (1,), 0, 60, 1),              # a single short sequence
+@pytest.mark.parametrize("ps", [16, 32, 64])
+@pytest.mark.parametrize("Hq,Hkv,ks,lo,hi,B,keys", [
+    (32, 4, (0, 1, 8, 16), 0, 300, 12, 32768),   # items without rows between others
+    (32, 4, (0, 4, 16), 0, 40, 60, 32768),       # fewer key blocks than workgroups
+    (32, 2, (16, 5, 0), 0, 700, 5, 32768),       # two 128-row items over the same keys
+    (16, 8, (1, 8), 480, 540, 64, 32768),        # shares around eight blocks
+    (16, 8, (1,), 0, 60, 1, 32768),              # a single short sequence
+    (16, 8, (1, 5), 900, 2500, 4, 2100),         # larger pages: about half the grid's partials fit the workspace
 ])
-def test_stream_k_with_a_wide_page_table(Hq, Hkv, ks, lo, hi, B):
+def test_stream_k_with_a_wide_page_table(Hq, Hkv, ks, lo, hi, B, keys, ps):
     """Short contexts under a page table sized for long ones: the planner goes
     by the table's width, so these batches take the stream-K split."""
-    b = _batch(Hq, Hkv, ks, lo, hi, 16, seed=64, B=B)
-    _check(b, page_table=_wide(b.models[0], 2048))
+    b = _batch(Hq, Hkv, ks, lo, hi, ps, seed=64, B=B)
+    _check(b, page_table=_wide(b.models[0], keys // ps))
