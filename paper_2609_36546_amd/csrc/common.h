@@ -114,4 +114,14 @@ __device__ __forceinline__ void dma16(const void* src, char* lds) {
                : "memory", "m0");
 }
 
+// The same from a wave-uniform base address and a 32-bit byte offset per lane,
+// to a wave-uniform LDS address: no per-lane 64-bit address arithmetic.
+__device__ __forceinline__ void dma16(const void* base, unsigned off, char* lds) {
+  const unsigned lds_addr = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(off), "s"(base)
+               : "memory", "m0");
+}
+
 }  // namespace ipdv

@@ -155,27 +155,46 @@ __device__ __forceinline__ constexpr int epi_off(int j) {
   return 32 * (j >> 4) + 8 * ((j >> 2) & 3) + (j & 3);
 }
 
-// Epilogue: per hidden row (lane column) and this wave's 128 vocabulary
-// entries, the group record (top-3 with indices, fourth value, s, e).  A lane
-// holds 64 of the group's entries for its row, in increasing vocabulary order
-// along j, so a later equal value never displaces an earlier one and the
+// Writes one group record.
+__device__ __forceinline__ void put_record(const LmParams& p, int m, int g, float v1, float v2, float v3,
+                                           float v4, int pos, const float (&sq)[4], float e) {
+  const size_t r = (size_t)m * p.rec_stride + g;
+  const bool some = v1 != -INFINITY;
+  p.rec_v1[r] = v1;
+  p.rec_v2[r] = v2;
+  p.rec_v3[r] = v3;
+  p.rec_v4[r] = v4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) p.rec_sq[q][r] = some ? sq[q] : 0.f;
+  p.rec_s[r] = some ? (sq[0] + sq[1]) + (sq[2] + sq[3]) : 0.f;
+  p.rec_e[r] = some ? e : 0.f;
+  p.rec_i[r] = pos;
+}
+
+// Epilogue: per hidden row (lane column) and this wave's 32 VB vocabulary
+// entries from v0 on, their top-3 with indices, fourth value, s and e: the
+// group record when the wave holds the whole group (VB = 4), half of one
+// when it holds 64 entries (VB = 2; `half` gets it, see lm_join_halves).  A
+// lane holds half of the wave's entries for its row, in increasing vocabulary
+// order along j, so a later equal value never displaces an earlier one and the
 // running top-4 needs no index comparisons: three medians of three and a
 // select keep the values, three compares and five selects the local indices.
-// The partner lane (l ^ 32) holds the other 64.  FULL: every entry of the tile
-// is < V (no masking).
-template <int RB, bool FULL>
-__device__ __forceinline__ void lm_epilogue(const LmParams& p, floatx16 (&acc)[4][RB], int vt, int m0,
-                                            int wv, int wr) {
+// The partner lane (l ^ 32) holds the other half.  FULL: every entry of the
+// tile is < V (no masking).
+template <int VB, int RB, bool FULL>
+__device__ __forceinline__ void lm_epilogue(const LmParams& p, floatx16 (&acc)[VB][RB], int v0, int m0,
+                                            floatx4* half) {
+  constexpr int NE = 16 * VB;                        // entries per lane and row
   const int lane = lane_id();
   const int h = lane >> 5;
-  const int vlane = vt * kVT + kGroup * wv + 4 * h;   // entry of local index 0
-  const int g = vt * (kVT / kGroup) + wv;
+  const int vlane = v0 + 4 * h;                      // entry of local index 0
+  const int g = v0 / kGroup;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
-    const int m = m0 + 32 * RB * wr + 32 * rb + (lane & 31);
+    const int m = m0 + 32 * rb + (lane & 31);
     if (!FULL) {
 #pragma unroll
-      for (int j = 0; j < 64; ++j)
+      for (int j = 0; j < NE; ++j)
         acc[j >> 4][rb][j & 15] = (vlane + epi_off(j) < p.V) ? acc[j >> 4][rb][j & 15] : -INFINITY;
     }
     float v1 = -INFINITY, v2 = -INFINITY, v3 = -INFINITY, v4 = -INFINITY;
@@ -184,7 +203,7 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, floatx16 (&acc)[4
     if (FULL) {
       // Values first: each entry is clamped into the sorted top-4.
 #pragma unroll
-      for (int j = 0; j < 64; ++j) {
+      for (int j = 0; j < NE; ++j) {
         const float x = acc[j >> 4][rb][j & 15];
         v4 = __builtin_amdgcn_fmed3f(v3, v4, x);
         v3 = __builtin_amdgcn_fmed3f(v2, v3, x);
@@ -206,7 +225,7 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, floatx16 (&acc)[4
       // the first entry holding each value is its index: a downward scan
       // keeps the lowest.
 #pragma unroll
-      for (int j = 63; j >= 0; --j) {
+      for (int j = NE - 1; j >= 0; --j) {
         const float x = acc[j >> 4][rb][j & 15];
         j1 = (x == v1) ? j : j1;
         j2 = (x == v2) ? j : j2;
@@ -218,7 +237,7 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, floatx16 (&acc)[4
       v1 = v2 = v3 = v4 = -INFINITY;
       j1 = j2 = j3 = 0;
 #pragma unroll
-      for (int j = 0; j < 64; ++j) {
+      for (int j = 0; j < NE; ++j) {
         const float x = acc[j >> 4][rb][j & 15];
         const bool c1 = x > v1, c2 = x > v2, c3 = x > v3;
         v4 = __builtin_amdgcn_fmed3f(v3, v4, x);
@@ -245,12 +264,12 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, floatx16 (&acc)[4
       top3_push(ov3, oi3, v1, i1, v2, i2, v3, i3, v4);
       v4 = fmaxf(v4, ov4);
     }
-    // v1 is now the group maximum; exp-sum and entropy numerator against it
+    // v1 is now the maximum; exp-sum and entropy numerator against it
     const float mub = ((v1 == -INFINITY) ? 0.f : v1) * kLog2e;
-    // block vb of the accumulators is the group's quarter vb (32 entries)
+    // block vb of the accumulators is a quarter of a group (32 entries)
     float sq[4] = {0.f, 0.f, 0.f, 0.f}, ee = 0.f;
 #pragma unroll
-    for (int j = 0; j < 64; ++j) {
+    for (int j = 0; j < NE; ++j) {
       const float x = acc[j >> 4][rb][j & 15];
       const float pe = fast_exp2(fmaf(x, kLog2e, -mub));
       sq[j >> 4] += pe;
@@ -260,50 +279,78 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, floatx16 (&acc)[4
         ee += (x != -INFINITY) ? pe * x : 0.f;
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sq[q] += lane_xor32(sq[q]);
+    for (int q = 0; q < VB; ++q) sq[q] += lane_xor32(sq[q]);
     ee += lane_xor32(ee);
-    if (h == 0 && m < p.M && g < p.n_groups) {
-      const size_t r = (size_t)m * p.rec_stride + g;
-      p.rec_v1[r] = v1;
-      p.rec_v2[r] = v2;
-      p.rec_v3[r] = v3;
-      p.rec_v4[r] = v4;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) p.rec_sq[q][r] = (v1 == -INFINITY) ? 0.f : sq[q];
-      p.rec_s[r] = (v1 == -INFINITY) ? 0.f : (sq[0] + sq[1]) + (sq[2] + sq[3]);
-      p.rec_e[r] = (v1 == -INFINITY) ? 0.f : ee;
-      const int gb = kGroup * g;   // the group's first entry
-      p.rec_i[r] = ((i1 - gb) & 127) | (((i2 - gb) & 127) << 7) | (((i3 - gb) & 127) << 14);
+    const int gb = kGroup * g;   // the group's first entry
+    const int pos = ((i1 - gb) & 127) | (((i2 - gb) & 127) << 7) | (((i3 - gb) & 127) << 14);
+    if constexpr (VB == 4) {
+      if (h == 0 && m < p.M && g < p.n_groups) put_record(p, m, g, v1, v2, v3, v4, pos, sq, ee);
+    } else if (h == 0) {
+      const int r = 2 * (32 * rb + (lane & 31));
+      half[r] = floatx4{v1, v2, v3, v4};
+      half[r + 1] = floatx4{__int_as_float(pos), sq[0], sq[1], ee};
     }
   }
 }
 
-template <int RB>
-__device__ __forceinline__ void lm_epilogue_any(const LmParams& p, floatx16 (&acc)[4][RB], int vt,
-                                                int m0, int wv, int wr) {
+template <int VB, int RB>
+__device__ __forceinline__ void lm_epilogue_any(const LmParams& p, floatx16 (&acc)[VB][RB], int vt, int v0,
+                                                int m0, floatx4* half) {
   if ((vt + 1) * kVT <= p.V)
-    lm_epilogue<RB, true>(p, acc, vt, m0, wv, wr);
+    lm_epilogue<VB, RB, true>(p, acc, v0, m0, half);
   else
-    lm_epilogue<RB, false>(p, acc, vt, m0, wv, wr);
+    lm_epilogue<VB, RB, false>(p, acc, v0, m0, half);
+}
+
+// The records of the groups gp < 2 of a tile of NM rows from the waves' halves
+// of them ([2 gp + half][row], two 16-byte words each): the upper half's
+// entries rank behind equal ones of the lower half, its sums are brought to
+// the group's maximum.
+template <int NM, int NT>
+__device__ __forceinline__ void lm_join_halves(const LmParams& p, const floatx4* half, int vt, int m0) {
+  for (int e = threadIdx.x; e < 2 * NM; e += NT) {
+    const int gp = e / NM, row = e % NM;
+    const int m = m0 + row, g = 2 * vt + gp;
+    if (m >= p.M || g >= p.n_groups) continue;
+    const floatx4 a = half[2 * (2 * gp * NM + row)], b = half[2 * (2 * gp * NM + row) + 1];
+    const floatx4 c = half[2 * ((2 * gp + 1) * NM + row)], d = half[2 * ((2 * gp + 1) * NM + row) + 1];
+    const int pa = __float_as_int(b[0]), pc = __float_as_int(d[0]);
+    float v1 = a[0], v2 = a[1], v3 = a[2], v4 = a[3];
+    auto ix = [](float v, int pos) { return v == -INFINITY ? 0x7fffffff : pos & 127; };
+    int i1 = ix(v1, pa), i2 = ix(v2, pa >> 7), i3 = ix(v3, pa >> 14);
+    top3_push(c[0], ix(c[0], pc), v1, i1, v2, i2, v3, i3, v4);
+    top3_push(c[1], ix(c[1], pc >> 7), v1, i1, v2, i2, v3, i3, v4);
+    top3_push(c[2], ix(c[2], pc >> 14), v1, i1, v2, i2, v3, i3, v4);
+    v4 = fmaxf(v4, c[3]);
+    const float fa = a[0] == -INFINITY ? 0.f : fast_exp2((a[0] - v1) * kLog2e);
+    const float fc = c[0] == -INFINITY ? 0.f : fast_exp2((c[0] - v1) * kLog2e);
+    const float sq[4] = {fa * b[1], fa * b[2], fc * d[1], fc * d[2]};
+    put_record(p, m, g, v1, v2, v3, v4, (i1 & 127) | ((i2 & 127) << 7) | ((i3 & 127) << 14), sq,
+               fa * b[3] + fc * d[3]);
+  }
 }
 
 // Tile number id.  The hardware deals workgroup ids to the 8 XCDs
 // round-robin (id % 8), and a persistent workgroup steps its tile number by
-// the grid size, a multiple of 8, so it stays on its XCD.  XCD x takes a
-// contiguous range of vocabulary tiles, and the row tiles of one vocabulary
-// tile run side by side on it: the W tile they share is fetched from HBM
-// once into that XCD's L2, and every 64-byte line of the group records (16
-// groups = 8 vocabulary tiles of one row) is completed inside one L2 before
-// it is written back.  A launch covers the vocabulary tiles vt_base ..
-// vt_base + n_vt_run - 1, as tile numbers below ceil(n_vt_run / 8) * 8 * n_rt;
-// the others are empty (false).
+// the grid size, a multiple of 8, so it stays on its XCD.  The tiles are
+// ordered by vocabulary tile, then row tile, and XCD x takes a contiguous
+// eighth of them: the row tiles of one vocabulary tile run side by side on
+// it, so the W tile they share is fetched from HBM once into that XCD's L2,
+// and every 64-byte line of the group records (16 groups = 8 vocabulary
+// tiles of one row) is completed inside one L2 before it is written back,
+// but for those at the seven seams.  The eighths differ by one tile at most
+// (whole vocabulary tiles per XCD put 33 of the 246 tiles left over at
+// M = 320 on two XCDs of 32 compute units, and so a second round).  A launch
+// covers the vocabulary tiles vt_base .. vt_base + n_vt_run - 1, as tile
+// numbers below 8 ceil(n_vt_run n_rt / 8); the others are empty (false).
 __device__ __forceinline__ bool gemm_tile(const LmParams& p, int id, int& vt, int& rt) {
   const int xcd = id & 7, local = id >> 3;
-  const int per = p.n_vt_run / 8, extra = p.n_vt_run % 8;
-  const int j = local / p.n_rt;
-  if (j >= per + (xcd < extra ? 1 : 0)) return false;
-  vt = p.vt_base + xcd * per + min(xcd, extra) + j;
-  rt = local % p.n_rt;
+  const int n = p.n_vt_run * p.n_rt;
+  const int per = n / 8, extra = n % 8;
+  if (local >= per + (xcd < extra ? 1 : 0)) return false;
+  const int t = xcd * per + min(xcd, extra) + local;
+  vt = p.vt_base + t / p.n_rt;
+  rt = t % p.n_rt;
   return true;
 }
 
@@ -395,7 +442,7 @@ __global__ __launch_bounds__(256) void lmhead_gemm_kernel(LmParams p) {
     if (more) store_stage((st + 1) & 1);
   }
 
-  lm_epilogue_any<RB>(p, acc, vt, m0, wv, wr);
+  lm_epilogue_any<4, RB>(p, acc, vt, v0 + kGroup * wv, m0 + 32 * RB * wr, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -414,39 +461,46 @@ constexpr int kDStage = 32;   // hidden channels per stage (64 bytes per row)
 
 __device__ __forceinline__ int dl_off(int r, int c) { return 64 * r + 16 * (c ^ ((r >> 2) & 3)); }
 
-template <int RB, int NBUF, int NW>
+template <int VB, int RB, int NBUF, int NW>
 __global__ __launch_bounds__(64 * NW) void lmhead_gemm_dlds_kernel(LmParams p) {
   static_assert(NBUF >= 3 && NBUF <= 5, "ring depth");
-  static_assert(NW == 4 || NW == 8, "2 x (NW / 2) waves");
+  static_assert(NW == 4 || NW == 8, "WV x WR waves");
+  constexpr int WV = kVT / (32 * VB), WR = NW / WV;
   int id = blockIdx.x, vt, rt;
   if (!gemm_tile(p, id, vt, rt)) return;
-  constexpr int NM = 32 * RB * (NW / 2);        // hidden rows per workgroup
+  constexpr int NM = 32 * RB * WR;              // hidden rows per workgroup
   constexpr int WB = kVT * 64;                  // W tile bytes per stage
   constexpr int SB = WB + NM * 64;              // stage bytes
   constexpr int NBLK = (kVT + NM) / 16;         // 1 KB load blocks per stage
-  constexpr int PW = NBLK / NW;                 // load instructions per wave and stage
+  constexpr int PW = (NBLK + NW - 1) / NW;      // load instructions per wave and stage
   constexpr int KS = kDStage / 16;              // MFMA k-steps per stage
-  static_assert(KS == 2 && (NBUF - 2) * PW <= 63 && NBLK % NW == 0, "pipeline shape");
+  static_assert(KS == 2 && (NBUF - 2) * PW <= 63, "pipeline shape");
   const int tid = threadIdx.x;
-  const int w = tid >> 6;
-  const int wv = w & 1, wr = w >> 1;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wv = w % WV, wr = w / WV;
   const int lane = lane_id();
   const int h = lane >> 5;
   const int rr = lane & 31;
   const int nst = p.Hd / kDStage;
 
-  __shared__ __attribute__((aligned(1024))) char s_ring[NBUF * SB];
+  // VB = 2: the joining of the waves' halves takes the last buffer's place (and a bit more)
+  constexpr int kHalves = VB == 2 ? 2 * WV * NM * (int)sizeof(floatx4) : 0;
+  constexpr int kLast = kHalves > SB ? kHalves : SB;
+  __shared__ __attribute__((aligned(1024))) char s_ring[(NBUF - 1) * SB + kLast];
 
   const bf16* Wp = reinterpret_cast<const bf16*>(p.W);
   const bf16* Hp = reinterpret_cast<const bf16*>(p.hidden_tiled);
   // This lane's source row and chunk for each of its load blocks, for tile
   // (vt_, rt_).
-  const bf16* src[PW];
+  unsigned src[PW];            // byte offsets from W (below 4 GiB), from the tile's hidden rows
+  const bf16* Ht = Hp;         // the tile's hidden rows
   auto set_src = [&](int vt_, int rt_) {
     const int m0 = rt_ * NM, v0 = vt_ * kVT;
+    const int mb_last = ((p.M + 15) >> 4) - 1 - (m0 >> 4);
+    Ht = Hp + (size_t)m0 * p.Hd;
 #pragma unroll
     for (int j = 0; j < PW; ++j) {
-      const int u = w + NW * j;
+      const int u = min(w + NW * j, NBLK - 1);   // past the last block: that one again
       const int r = (u < kVT / 16 ? 16 * u : 16 * (u - kVT / 16)) + (lane >> 2);
       const int c = (lane & 3) ^ ((r >> 2) & 3);
       if (u < kVT / 16) {
@@ -455,16 +509,16 @@ __global__ __launch_bounds__(64 * NW) void lmhead_gemm_dlds_kernel(LmParams p) {
           // the same row and (swizzled) chunk as in the row-major case, so the
           // LDS image is identical.  Blocks past V: any valid block, masked later.
           const int vb = min((v0 >> 4) + u, ((p.V + 15) >> 4) - 1);
-          src[j] = Wp + (size_t)vb * (p.Hd >> 5) * 512 + (lane >> 2) * 32 + 8 * c;
+          src[j] = (unsigned)vb * ((unsigned)p.Hd >> 5) * 1024 + (lane >> 2) * 64 + 16 * c;
         } else {
           const int v = min(v0 + r, p.V - 1);     // rows past V: any valid row, masked later
-          src[j] = Wp + (size_t)v * p.Hd + 8 * c;
+          src[j] = (unsigned)v * (unsigned)p.Hd * 2 + 16 * c;
         }
       } else {
         // hidden rows come from the per-call copy in the same 16-row x 32-channel
         // block layout (rows past M there are zero and never stored)
-        const int mb = min((m0 >> 4) + (u - kVT / 16), ((p.M + 15) >> 4) - 1);
-        src[j] = Hp + (size_t)mb * (p.Hd >> 5) * 512 + (lane >> 2) * 32 + 8 * c;
+        const int mb = min(u - kVT / 16, mb_last);
+        src[j] = (unsigned)mb * ((unsigned)p.Hd >> 5) * 1024 + (lane >> 2) * 64 + 16 * c;
       }
     }
   };
@@ -479,32 +533,36 @@ __global__ __launch_bounds__(64 * NW) void lmhead_gemm_dlds_kernel(LmParams p) {
   auto dma = [&](int st, int j0, int j1) {
     char* buf = s_ring + (st % NBUF) * SB;
     const int k0 = min(st, nst - 1) * kDStage;
+    const bf16* wb = Wp + wk * k0;
+    const bf16* hb = Ht + 16 * k0;
 #pragma unroll
     for (int j = j0; j < j1; ++j)
-      dma16(src[j] + (j < kVT / (16 * NW) ? wk : 16) * k0, buf + 1024 * (w + NW * j));
+      dma16(j < kVT / (16 * NW) ? wb : hb, src[j], buf + 1024 * min(w + NW * j, NBLK - 1));
   };
   // Operand offsets of this lane within a stage.  Chunk 2 ks + h of a row sits
   // at 16 ((2 ks + h) ^ q), q = row bits 2-3, which is the ks = 0 offset xor
   // 32 ks; 32-row steps keep q.
-  const int a_off = dl_off(128 * wv + rr, h);
+  const int a_off = dl_off(32 * VB * wv + rr, h);
   const int b_off = WB + dl_off(32 * RB * wr + rr, h);
-  bf16x8 fa[2][4], fb[2][RB];
+  bf16x8 fa[2][VB], fb[2][RB];
   auto load = [&](int set, const char* buf, int ks) {
     const int x = 32 * ks;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
-      fb[set][rb] = *reinterpret_cast<const bf16x8*>(buf + ((b_off + 2048 * rb) ^ x));
+      fb[set][rb] = *reinterpret_cast<const bf16x8*>(buf + (b_off ^ x) + 2048 * rb);
 #pragma unroll
-    for (int vb = 0; vb < 4; ++vb)
-      fa[set][vb] = *reinterpret_cast<const bf16x8*>(buf + ((a_off + 2048 * vb) ^ x));
+    for (int vb = 0; vb < VB; ++vb)
+      fa[set][vb] = *reinterpret_cast<const bf16x8*>(buf + (a_off ^ x) + 2048 * vb);
   };
 
-  floatx16 acc[4][RB];
-  // MFMAs of operand set `set` over vocabulary block vb.
-  auto mma = [&](int set, int vb) {
+  floatx16 acc[VB][RB];
+  // Quarter q of the MFMAs of operand set `set`.
+  auto mma = [&](int set, int q) {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+    for (int i = q * VB * RB / 4; i < (q + 1) * VB * RB / 4; ++i) {
+      const int vb = i / RB, rb = i % RB;
       acc[vb][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][vb], fb[set][rb], acc[vb][rb], 0, 0, 0);
+    }
   };
 #define IPDV_SB __builtin_amdgcn_sched_barrier(0)
 
@@ -542,7 +600,7 @@ __global__ __launch_bounds__(64 * NW) void lmhead_gemm_dlds_kernel(LmParams p) {
     asm volatile("" ::: "memory");
     load(0, s_ring, 0);
 #pragma unroll
-    for (int vb = 0; vb < 4; ++vb)
+    for (int vb = 0; vb < VB; ++vb)
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -596,14 +654,25 @@ __global__ __launch_bounds__(64 * NW) void lmhead_gemm_dlds_kernel(LmParams p) {
     const int vt_done = vt, m0_done = rt * NM;
     id += gridDim.x;
     const bool more = gemm_tile(p, id, vt, rt);
-    if (more) {
+    if (more || VB == 2) {
       __builtin_amdgcn_s_barrier();   // every wave is done with the ring
       asm volatile("" ::: "memory");
+    }
+    if (more) {
       set_src(vt, rt);
 #pragma unroll
       for (int s0 = 0; s0 < NBUF - 1; ++s0) dma(s0, 0, PW);
     }
-    lm_epilogue_any<RB>(p, acc, vt_done, m0_done, wv, wr);
+    // (NBUF - 1) * SB: past the stages that the next tile's first loads fill
+    floatx4* halves = reinterpret_cast<floatx4*>(s_ring + (NBUF - 1) * SB);
+    lm_epilogue_any<VB, RB>(p, acc, vt_done, vt_done * kVT + 32 * VB * wv, m0_done + 32 * RB * wr,
+                            halves + 2 * (NM * wv + 32 * RB * wr));
+    if constexpr (VB == 2) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      lm_join_halves<NM, 64 * NW>(p, halves, vt_done, m0_done);
+    }
     if (!more) break;
     // the load addresses again, rather than held in registers across the epilogue
     set_src(vt, rt);
@@ -1296,12 +1365,12 @@ __global__ __launch_bounds__(kMT) void sample_kernel(LmParams p, SampleParams s)
 
 // GEMM launch per input type: bf16 takes the direct-to-LDS kernel when the
 // hidden size is a multiple of four stages, fp32 the register-staged one.
-dim3 gemm_grid(const LmParams& p) { return dim3((p.n_vt_run + 7) / 8 * 8 * p.n_rt); }
+dim3 gemm_grid(const LmParams& p) { return dim3((p.n_vt_run * p.n_rt + 7) / 8 * 8); }
 
 // Launch of the persistent direct-to-LDS GEMM: as many workgroups as the
 // device holds at once (cached per device; a multiple of 8, so that each
 // stays on its XCD), but no more than there are tile numbers.
-template <int RB, int NBUF, int NW>
+template <int VB, int RB, int NBUF, int NW>
 void launch_dlds(const LmParams& q, hipStream_t st) {
   static int slots[64] = {};
   int dev = 0;
@@ -1310,7 +1379,7 @@ void launch_dlds(const LmParams& q, hipStream_t st) {
   if (n == 0) {
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void*>(&lmhead_gemm_dlds_kernel<RB, NBUF, NW>), 64 * NW, 0) !=
+            &per_cu, reinterpret_cast<const void*>(&lmhead_gemm_dlds_kernel<VB, RB, NBUF, NW>), 64 * NW, 0) !=
             hipSuccess ||
         per_cu < 1)
       per_cu = 1;
@@ -1318,14 +1387,17 @@ void launch_dlds(const LmParams& q, hipStream_t st) {
     if (dev >= 0) slots[dev] = n;
   }
   const dim3 grid((unsigned)min((int)gemm_grid(q).x, n));
-  hipLaunchKernelGGL((lmhead_gemm_dlds_kernel<RB, NBUF, NW>), grid, dim3(64 * NW), 0, st, q);
+  hipLaunchKernelGGL((lmhead_gemm_dlds_kernel<VB, RB, NBUF, NW>), grid, dim3(64 * NW), 0, st, q);
 }
 
 template <int RB>
 void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
   // 64 * RB hidden rows per workgroup.  256 and 128 rows take eight waves
-  // (two per SIMD, each 128 vocabulary entries x 32 * RB / 2 rows), 64 and
-  // 192 rows four.  The direct-to-LDS kernels read the hidden rows from a
+  // (two per SIMD) of 128 vocabulary entries x 32 * RB / 2 rows; 320 rows, and
+  // 192 where there are several row tiles, eight waves of 64 entries x 32 RB
+  // rows (320 rows as 128-entry waves would be 80 rows each, no multiple of
+  // 32), whose half records are joined through LDS; 64 rows, and 192 in a
+  // single row tile, four waves.  The direct-to-LDS kernels read the hidden rows from a
   // copy in W's tiled block layout, written first into the workspace, so
   // that every operand load reads whole cache lines.
   // Hd is a multiple of 64 (the host checks), so of the 32-channel stage.
@@ -1334,8 +1406,13 @@ void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
                      reinterpret_cast<const bf16*>(p.hidden), p.M, p.Hd,
                      reinterpret_cast<bf16*>(const_cast<void*>(p.hidden_tiled)), n_chunks);
   trace_mark(st);   // the hidden copy's interval ends here; the GEMM's begins
-  if constexpr (RB == 4) {
-    // With one row tile (M <= 256): 256-row tiles for as many whole rounds
+  if (RB == 3 && p.n_rt == 1) {
+    // Each W tile is read by one compute unit alone: three rounds of four
+    // waves (a third fewer LDS reads than eight half-group waves), no second
+    // launch: M = 192 183 us against 206.
+    launch_dlds<4, 3, 4, 4>(p, st);
+  } else if constexpr (RB >= 3) {
+    // With one row tile (M <= 320): full-row tiles for as many whole rounds
     // of one tile per compute unit as the vocabulary fills; the vocabulary
     // tiles left over for a last, partial round run as 128-row tiles in a
     // second launch, which spreads that round's work over twice as many
@@ -1348,18 +1425,21 @@ void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
     if (n_main > 0) {
       q.vt_base = 0;
       q.n_vt_run = n_main;
-      launch_dlds<2, 4, 8>(q, st);
+      if constexpr (RB == 4)
+        launch_dlds<4, 2, 4, 8>(q, st);
+      else
+        launch_dlds<2, RB, 4, 8>(q, st);
     }
     if (n_main < p.n_vt) {
       q.vt_base = n_main;
       q.n_vt_run = p.n_vt - n_main;
       q.n_rt = (p.M + 127) / 128;
-      launch_dlds<1, 4, 8>(q, st);
+      launch_dlds<4, 1, 4, 8>(q, st);
     }
   } else if constexpr (RB == 2)
-    launch_dlds<1, 4, 8>(p, st);
+    launch_dlds<4, 1, 4, 8>(p, st);
   else
-    launch_dlds<RB, 4, 4>(p, st);
+    launch_dlds<4, RB, 4, 4>(p, st);
 }
 
 template <int RB>
@@ -1403,11 +1483,32 @@ LmPlan lm_plan(int M, int Hd, int V, int K, bool bf16) {
   LmPlan pl{};
   pl.n_groups = (V + kGroup - 1) / kGroup;
   pl.n_vt = (V + kVT - 1) / kVT;
-  // 64*RB hidden rows per workgroup (RB <= 4); fp32 keeps RB = 1 so that its
-  // double-buffered stage fits the LDS.
-  const int rows = M < 256 ? M : 256;
-  pl.rb = rows <= 64 ? 1 : rows <= 128 ? 2 : rows <= 192 ? 3 : 4;
-  if (!bf16) pl.rb = 1;
+  // 64*RB hidden rows per workgroup; fp32 keeps RB = 1 so that its
+  // double-buffered stage fits the LDS.  bf16 above 64 rows takes the row
+  // tile with the least time by rounds of one tile per compute unit (256),
+  // in us per round at Hd = 2048 (kRoundUs; the ratios hold for other Hd: the
+  // epilogue is a sixth).  One row tile of 256 or 320 rows runs its last,
+  // partial round as 128-row tiles in a second launch (launch_gemm).
+  // Measured at V = 151936 with tiles of at most 256 rows / as chosen here:
+  // M = 320 318 / 239 us (two tiles of 256 did 512 rows of work), M = 384
+  // 320 / 281, M = 512 332 / 331 (256-row tiles either way).
+  static constexpr int kRoundUs[6] = {0, 0, 42, 54, 62, 77};
+  pl.rb = 1;
+  if (bf16 && M > 64) {
+    long best = 0;
+    for (int rb = 2; rb <= 5; ++rb) {
+      const long n_rt = (M + 64L * rb - 1) / (64 * rb), n_vt = pl.n_vt;
+      long us = (n_vt * n_rt + 255) / 256 * kRoundUs[rb];
+      if (rb >= 4 && n_rt == 1) {
+        const long left = n_vt % 256;
+        us = n_vt / 256 * kRoundUs[rb] + (left ? (left * ((M + 127) / 128) + 255) / 256 * kRoundUs[2] + 5 : 0);
+      }
+      if (rb == 2 || us < best) {
+        best = us;
+        pl.rb = rb;
+      }
+    }
+  }
   pl.n_rt = (M + 64 * pl.rb - 1) / (64 * pl.rb);
   pl.rec_stride = (pl.n_groups + 3) / 4 * 4;
   const size_t recs = (size_t)M * pl.rec_stride;
@@ -1470,7 +1571,8 @@ hipError_t launch_lmhead(const LmLaunch& L, const LmPlan& pl, hipStream_t st) {
       case 1: return launch_rb<bf16, 1>(p, st);
       case 2: return launch_rb<bf16, 2>(p, st);
       case 3: return launch_rb<bf16, 3>(p, st);
-      default: return launch_rb<bf16, 4>(p, st);
+      case 4: return launch_rb<bf16, 4>(p, st);
+      default: return launch_rb<bf16, 5>(p, st);
     }
   }
   return launch_rb<float, 1>(p, st);

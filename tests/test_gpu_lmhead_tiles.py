@@ -1,0 +1,84 @@
+"""GPU parity of the LM head for every row tile that the planner can choose
+(192 and 320 rows, one and several of them), against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_36546_amd import ops
+from tests import parity
+from tests.workload import to_np
+
+pytestmark = pytest.mark.gpu
+
+FULL = 257 * 256          # vocabulary tiles for one whole round of 256, and one more
+
+
+def _case(M, V, Hd, seed, dup=False):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    h = torch.randn(M, Hd, generator=gen, device="cuda")
+    h = (h / h.pow(2).mean(1, keepdim=True).sqrt()).to(torch.bfloat16)
+    W = (torch.randn(V, Hd, generator=gen, device="cuda") * 0.1).to(torch.bfloat16)
+    if dup:
+        # equal logits on both sides of the middle of record groups (entries 63 | 64)
+        for g in range(0, V // 128, 3):
+            W[128 * g + 64] = W[128 * g + 63]
+    prop = np.random.default_rng(seed).integers(0, V, size=M)
+    return h, W, prop
+
+
+@pytest.mark.parametrize("M", [129, 192, 250, 257, 320, 321, 384, 600])
+@pytest.mark.parametrize("last", [208, 64, 130])
+def test_row_tiles(M, last):
+    """192 rows (M = 129, 192: four waves; 384: eight waves, two tiles), 256
+    (250), 320 (257, 320; 600: two tiles), each with a last vocabulary tile
+    that ends inside a half group, at its end, or two entries into a group."""
+    V, K = FULL + last, 16
+    h, W, prop = _case(M, V, 128, M + last, dup=True)
+    print(f"[lmhead tiles] M={M} V={V}", flush=True)
+    g = ops.lmhead_logsoftmax_verify(h, W, torch.from_numpy(prop.astype(np.int32)).cuda(), K)
+    rows = np.unique(np.r_[0, 31, 32, 63, 64, 127, 128, M // 2, M - 2, M - 1, np.arange(0, M, 29)])
+    rows = rows[rows < M]
+    logits = oracle.logits_fp64(to_np(h)[rows], to_np(W))
+    ref = oracle.lmhead_logsoftmax(None, None, prop[rows], K, logits=logits)
+    parity.check_lmhead(g, ref, logits, K, rows=rows)
+    # equal logits rank by index: a duplicate follows its original directly
+    gi = to_np(g["topk_idx"]).astype(np.int64)[rows]
+    for r in gi:
+        for i in np.nonzero((r % 128 == 64) & (r // 128 % 3 == 0) & (r < V - 128))[0]:
+            assert i > 0 and r[i - 1] == r[i] - 1, r
+    packed = ops.lmhead_pack_w(W)
+    t = ops.lmhead_logsoftmax_verify(h, packed, torch.from_numpy(prop.astype(np.int32)).cuda(), K)
+    for key in ("lse", "logp_prop", "argmax", "topk_idx", "topk_logp", "entropy"):
+        assert torch.equal(g[key], t[key]), key
+
+
+@pytest.mark.parametrize("M", [300, 384])
+def test_uniform_logits_join_halves(M):
+    """W = 0: every logit ties, within and across the joined half groups."""
+    V, K = FULL + 3, 32
+    h = torch.ones(M, 64, device="cuda", dtype=torch.bfloat16)
+    W = torch.zeros(V, 64, device="cuda", dtype=torch.bfloat16)
+    prop = torch.zeros(M, dtype=torch.int32, device="cuda")
+    g = ops.lmhead_logsoftmax_verify(h, W, prop, K)
+    np.testing.assert_array_equal(to_np(g["topk_idx"]), np.tile(np.arange(K), (M, 1)))
+    np.testing.assert_allclose(to_np(g["lse"]), np.log(V), atol=1e-4)
+    np.testing.assert_allclose(to_np(g["entropy"]), np.log(V), atol=1e-3)
+
+
+def test_draws_from_joined_records():
+    """The draw reads the quarter sums of the joined halves: each token's
+    interval in the fp64 CDF holds u within the draw's stated 1e-5."""
+    M, V = 320, FULL + 100
+    h, W, prop = _case(M, V, 64, 5)
+    h = h * 4
+    ws = torch.empty(ops.lmhead_workspace_size(M, 64, V, 8), dtype=torch.uint8, device="cuda")
+    ops.lmhead_logsoftmax_verify(h, W, torch.from_numpy(prop.astype(np.int32)).cuda(), 8, workspace=ws)
+    u = torch.linspace(0, 0.9999, M, device="cuda")
+    tok = to_np(ops.lmhead_sample(h, W, 8, ws, u)).astype(np.int64)
+    p = torch.softmax(h.double() @ W.double().t(), 1)
+    c = torch.cumsum(p, 1).cpu().numpy()
+    for m in range(M):
+        lo = c[m, tok[m] - 1] if tok[m] > 0 else 0.0
+        assert lo - 1e-5 <= float(u[m]) <= c[m, tok[m]] + 1e-5, m
