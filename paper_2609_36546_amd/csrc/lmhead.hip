@@ -682,6 +682,146 @@ __global__ __launch_bounds__(64 * NW) void lmhead_gemm_dlds_kernel(LmParams p) {
 }
 
 // ---------------------------------------------------------------------------
+// Few rows (M <= 64, bf16): the same product as a stream of W.
+//
+// HBM bounds it (622 MB of W at V = 151936, Hd = 2048: 109 us at 5.7 TB/s), so
+// what counts is whole cache lines, bytes in flight and an even end.  A stage
+// is 64 channels, so that a row-major W is read in whole 128-byte lines too.
+// A workgroup owns WV record groups of 128 entries and 64 rows, two waves per
+// group (32 rows each), three stages in LDS; one or two workgroups share a
+// compute unit.  The grid is the tile count over whole rounds, so that every
+// workgroup walks the same number of tiles.  Hidden rows are read where they
+// are, without a copy; two groups per workgroup halve that traffic out of L2
+// (256 KB per tile at 64 rows).  Calls at V = 151936, Hd = 2048, us, the
+// kernel above with 64-row tiles / this one, row-major W, then tiled:
+// M = 1 158 / 120, 127 / 116; M = 64 162 / 127, 132 / 123.
+//
+// LDS rows are 128 bytes; chunk c of row r sits at c ^ (r / 2) % 8, which puts
+// the 16 rows a 16-byte LDS read serves at once (lanes 0-3, 12-15, 20-27; the
+// others of 32) in distinct bank groups.
+// ---------------------------------------------------------------------------
+constexpr int kSStage = 64;   // hidden channels per stage
+constexpr int kSRows = 64;    // hidden rows per workgroup
+constexpr int kSBuf = 3;
+
+template <int WV>                                   // record groups per workgroup
+__global__ __launch_bounds__(128 * WV, 1) void lmhead_gemm_stream_kernel(LmParams p) {
+  constexpr int NW = 2 * WV;
+  constexpr int NV = kGroup * WV;
+  constexpr int WB = NV * 128;                      // W bytes per stage
+  constexpr int SB = WB + kSRows * 128;
+  constexpr int NWB = NV / 8, NBLK = NWB + kSRows / 8;   // load blocks: 8 rows x 128 bytes
+  constexpr int PW = NBLK / NW;
+  static_assert(NWB % NW == 0 && NBLK % NW == 0 && (kSBuf - 1) * PW <= 63, "pipeline shape");
+  int id = blockIdx.x, vt, rt;
+  if (!gemm_tile(p, id, vt, rt)) return;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wv = w % WV, wr = w / WV;               // this wave's group and rows 32 wr ..
+  const int lane = lane_id();
+  const int h = lane >> 5, rr = lane & 31;
+  const int nst = p.Hd / kSStage;
+  __shared__ __attribute__((aligned(1024))) char s_ring[kSBuf * SB];
+  const char* Wp = reinterpret_cast<const char*>(p.W);
+  const char* Hp = reinterpret_cast<const char*>(p.hidden);
+
+  unsigned src[PW];           // byte offsets from W (below 4 GiB) and from the hidden rows
+  auto set_src = [&](int vt_) {
+#pragma unroll
+    for (int j = 0; j < PW; ++j) {
+      const int u = w + NW * j;
+      const int r = 8 * (u < NWB ? u : u - NWB) + (lane >> 3);
+      const int c = (lane & 7) ^ ((r >> 1) & 7);
+      if (j < NWB / NW) {
+        if (p.w_tiled) {
+          const int vb = min((vt_ * NV + r) >> 4, ((p.V + 15) >> 4) - 1);   // past V: masked later
+          src[j] = ((unsigned)vb * ((unsigned)p.Hd >> 5) + (c >> 2)) * 1024 + (r & 15) * 64 + 16 * (c & 3);
+        } else {
+          src[j] = (unsigned)min(vt_ * NV + r, p.V - 1) * (unsigned)p.Hd * 2 + 16 * c;
+        }
+      } else {
+        src[j] = (unsigned)min(r, p.M - 1) * (unsigned)p.Hd * 2 + 16 * c;      // past M: never stored
+      }
+    }
+  };
+  set_src(vt);
+  const int ws = p.w_tiled ? 2048 : 128;            // bytes a stage advances in W
+  // Rows a multiple of 4 KB apart lie on the same memory channel, and so do the
+  // lines a stage reads of all of them; workgroups that start together would
+  // ask the same channels.  Each pair of groups therefore starts its sum at a
+  // stage of its own (row-major W at Hd = 2048: 139 -> 120 us of call at M = 1;
+  // other Hd gain nothing or lose 5%).  The order depends on the group alone,
+  // so both layouts of W give the same bits.
+  const bool turn = p.Hd % 2048 == 0;
+  int rot = turn ? vt * WV / 2 % nst : 0;
+  // Stages past the end reload the last one into a free buffer, so that every
+  // wait has the same count.
+  auto dma = [&](int st) {
+    char* buf = s_ring + (st % kSBuf) * SB;
+    int s = min(st, nst - 1) + rot;
+    if (s >= nst) s -= nst;
+    const char* wb = Wp + (size_t)s * ws;
+    const char* hb = Hp + (size_t)s * 128;
+#pragma unroll
+    for (int j = 0; j < PW; ++j) dma16(j < NWB / NW ? wb : hb, src[j], buf + 1024 * (w + NW * j));
+  };
+  const int a_off = 128 * (kGroup * wv + rr) + 16 * (h ^ ((rr >> 1) & 7));
+  const int b_off = WB + 128 * (32 * wr + rr) + 16 * (h ^ ((rr >> 1) & 7));
+
+#pragma unroll
+  for (int s0 = 0; s0 < kSBuf - 1; ++s0) dma(s0);
+  bool first = true;
+  for (;;) {
+    floatx16 acc[4][1];
+#pragma unroll
+    for (int vb = 0; vb < 4; ++vb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[vb][0][e] = 0.f;
+    for (int st = 0; st < nst; ++st) {
+      // stage st has landed (the next one may be in flight; after an epilogue
+      // its record stores are too, and loads and stores are not promised to
+      // complete in issue order: a full wait), and every wave has read stage
+      // st - 1, whose buffer the refill takes
+      if (first || st > 0)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((kSBuf - 2) * PW) : "memory");
+      else
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      dma(st + kSBuf - 1);
+      const char* buf = s_ring + (st % kSBuf) * SB;
+#pragma unroll
+      for (int ks = 0; ks < kSStage / 16; ++ks) {
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(buf + (b_off ^ (32 * ks)));
+#pragma unroll
+        for (int vb = 0; vb < 4; ++vb) {
+          const bf16x8 a = *reinterpret_cast<const bf16x8*>(buf + (a_off ^ (32 * ks)) + 4096 * vb);
+          acc[vb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[vb][0], 0, 0, 0);
+        }
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // the reloads past the end
+    const int v_done = vt * NV + kGroup * wv;
+    id += gridDim.x;
+    const bool more = gemm_tile(p, id, vt, rt);
+    if (more) {
+      __builtin_amdgcn_s_barrier();   // every wave is done with the ring
+      asm volatile("" ::: "memory");
+      set_src(vt);
+      rot = turn ? vt * WV / 2 % nst : 0;
+#pragma unroll
+      for (int s0 = 0; s0 < kSBuf - 1; ++s0) dma(s0);
+    }
+    if (v_done + kGroup <= p.V)
+      lm_epilogue<4, 1, true>(p, acc, v_done, 32 * wr, nullptr);
+    else if (v_done < p.V)
+      lm_epilogue<4, 1, false>(p, acc, v_done, 32 * wr, nullptr);
+    if (!more) break;
+    set_src(vt);   // again, rather than held in registers across the epilogue
+    first = false;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Merge: one workgroup (256 threads) per row.
 // ---------------------------------------------------------------------------
 
@@ -1367,27 +1507,43 @@ __global__ __launch_bounds__(kMT) void sample_kernel(LmParams p, SampleParams s)
 // hidden size is a multiple of four stages, fp32 the register-staged one.
 dim3 gemm_grid(const LmParams& p) { return dim3((p.n_vt_run * p.n_rt + 7) / 8 * 8); }
 
+// Workgroups of a kernel that the current device holds at once (cached per
+// device and kernel), a multiple of 8, so that a persistent one stays on its XCD.
+int resident_slots(int (&cache)[64], const void* kernel, int threads) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
+  int n = dev >= 0 ? cache[dev] : 0;
+  if (n == 0) {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1)
+      per_cu = 1;
+    n = max(8, device_cus() * per_cu / 8 * 8);
+    if (dev >= 0) cache[dev] = n;
+  }
+  return n;
+}
+
 // Launch of the persistent direct-to-LDS GEMM: as many workgroups as the
-// device holds at once (cached per device; a multiple of 8, so that each
-// stays on its XCD), but no more than there are tile numbers.
+// device holds at once, but no more than there are tile numbers.
 template <int VB, int RB, int NBUF, int NW>
 void launch_dlds(const LmParams& q, hipStream_t st) {
   static int slots[64] = {};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
-  int n = dev >= 0 ? slots[dev] : 0;
-  if (n == 0) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void*>(&lmhead_gemm_dlds_kernel<VB, RB, NBUF, NW>), 64 * NW, 0) !=
-            hipSuccess ||
-        per_cu < 1)
-      per_cu = 1;
-    n = max(8, device_cus() * per_cu / 8 * 8);
-    if (dev >= 0) slots[dev] = n;
-  }
+  const int n = resident_slots(
+      slots, reinterpret_cast<const void*>(&lmhead_gemm_dlds_kernel<VB, RB, NBUF, NW>), 64 * NW);
   const dim3 grid((unsigned)min((int)gemm_grid(q).x, n));
   hipLaunchKernelGGL((lmhead_gemm_dlds_kernel<VB, RB, NBUF, NW>), grid, dim3(64 * NW), 0, st, q);
+}
+
+// Launch of the few-row stream: the groups over whole rounds of the device.
+template <int WV>
+void launch_stream(LmParams q, hipStream_t st) {
+  static int slots[64] = {};
+  const int n = resident_slots(slots, reinterpret_cast<const void*>(&lmhead_gemm_stream_kernel<WV>), 128 * WV);
+  q.n_vt_run = (q.n_groups + WV - 1) / WV;
+  q.n_rt = 1;
+  const int rounds = (q.n_vt_run + n - 1) / n;
+  const int grid = ((q.n_vt_run + rounds - 1) / rounds + 7) / 8 * 8;
+  hipLaunchKernelGGL(lmhead_gemm_stream_kernel<WV>, dim3((unsigned)grid), dim3(128 * WV), 0, st, q);
 }
 
 template <int RB>
@@ -1401,6 +1557,19 @@ void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
   // copy in W's tiled block layout, written first into the workspace, so
   // that every operand load reads whole cache lines.
   // Hd is a multiple of 64 (the host checks), so of the 32-channel stage.
+  // Few rows stream W instead, reading the hidden rows in place, for which
+  // these must start on a 16-byte boundary.
+  if (RB == 1 && (reinterpret_cast<uintptr_t>(p.hidden) & 15) == 0) {
+    trace_mark(st);   // no hidden copy: an empty interval
+    // Two groups per workgroup where all the compute units get one, but for
+    // the fewest rows (M = 1 120 us with one, 121 with two; M = 24 129 and
+    // 125; M = 2, V = 32003 37 and 42).
+    if (p.n_groups <= 2 * device_cus() || p.M <= 8)
+      launch_stream<1>(p, st);
+    else
+      launch_stream<2>(p, st);
+    return;
+  }
   const size_t n_chunks = (size_t)((p.M + 15) / 16) * 16 * p.Hd / 8;
   hipLaunchKernelGGL(pack_w_kernel, dim3((unsigned)((n_chunks + 255) / 256)), dim3(256), 0, st,
                      reinterpret_cast<const bf16*>(p.hidden), p.M, p.Hd,

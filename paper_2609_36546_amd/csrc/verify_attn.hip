@@ -1579,7 +1579,7 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
   // (stream-K).  A tile walks its keys at 0.75 us per 32-key block however
   // many tiles there are, up to about one per compute unit; stream-K spreads
   // every item over the chip but pays its tables, the partials and the
-  // combine (9 us at 64-row items, 14 us at 128-row ones), and every item of
+  // combine (9 us where that exceeds the call itself), and every item of
   // a window appends it again (0.03 us per window row).  By the host's bounds
   // of keys and rows, measured on both sides of the line (us, tile / stream-K):
   //   64 teacher windows of 8 rows, contexts to 300 / 1000 / 8192: 16 / 24,
@@ -1589,7 +1589,7 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
   // More items than the stream-K tables hold, with more than 64 rows each,
   // fill the chip as tiles at any length (eight prompts of 512-1024 tokens:
   // register kernel 484 us, tiles 82 us).
-  const double fixed = (pl.sk_qt == 2 ? 14 : 9) + 0.03 * max_q;
+  const double fixed = 9 + 0.03 * max_q;
   if (D == 128 && (0.75 * maxblk <= fixed + 0.002 * std::min(n_it, 256L) * maxblk ||
                    (!pl.sk && n_it >= kSkGrid && rows > kRows)))
     pl.tile = pl.sk_qt;

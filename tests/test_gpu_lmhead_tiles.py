@@ -82,3 +82,29 @@ def test_draws_from_joined_records():
     for m in range(M):
         lo = c[m, tok[m] - 1] if tok[m] > 0 else 0.0
         assert lo - 1e-5 <= float(u[m]) <= c[m, tok[m]] + 1e-5, m
+
+
+@pytest.mark.parametrize("M,V,Hd", [
+    (1, 130, 64),             # one stage; the second group has two entries
+    (8, 66000, 2048),         # one group per workgroup, its sum turned by the group
+    (9, 66000, 2048),         # two groups per workgroup
+    (33, 65792 + 128, 128),   # two groups per workgroup, the last workgroup with one
+    (64, 65792 + 129, 192),   # and with one group and an entry
+    (64, 5003, 4096),
+])
+def test_few_rows(M, V, Hd):
+    h, W, prop = _case(M, V, Hd, M + V, dup=True)
+    print(f"[lmhead tiles] M={M} V={V} Hd={Hd}", flush=True)
+    K = min(16, V)
+    p = torch.from_numpy(prop.astype(np.int32)).cuda()
+    g = ops.lmhead_logsoftmax_verify(h, W, p, K)
+    logits = oracle.logits_fp64(to_np(h), to_np(W))
+    parity.check_lmhead(g, oracle.lmhead_logsoftmax(None, None, prop, K, logits=logits), logits, K)
+    t = ops.lmhead_logsoftmax_verify(h, ops.lmhead_pack_w(W), p, K)
+    # hidden rows off a 16-byte boundary take the copy and the 64-row tiles
+    off = torch.empty(h.numel() + 4, dtype=h.dtype, device="cuda")[4:].view(h.shape)
+    off.copy_(h)
+    o = ops.lmhead_logsoftmax_verify(off, W, p, K)
+    for key in ("lse", "logp_prop", "argmax", "topk_idx", "topk_logp", "entropy"):
+        assert torch.equal(g[key], t[key]), key
+    parity.check_lmhead(o, oracle.lmhead_logsoftmax(None, None, prop, K, logits=logits), logits, K)
