@@ -55,6 +55,16 @@ struct LmParams {
   int w_tiled;        // W in 16-row x 32-channel blocks (lmhead_pack_w), else [V][Hd]
   int n_groups, n_rt, n_vt;
   int rec_stride;          // record entries per row: n_groups rounded up to a multiple of 4
+  // Rows of W a multiple of 4 KB apart lie on the same memory channel, and so
+  // do the lines that a stage reads of all of them: workgroups that start
+  // together would all ask the same channels.  With `turn` each vocabulary
+  // tile starts its sum over the channels at a stage of its own.  Set for Hd a
+  // multiple of 2048 and one row tile of at most 256 rows, where W bounds the
+  // product.  Calls with a row-major W at V = 151936, Hd = 2048, us: M = 1
+  // 139 -> 120, M = 128 183 -> 166, M = 256 222 -> 202 (M = 320 256 -> 248, but
+  // 1% slower with tiled W; M = 512 336 -> 343; Hd = 1024 5% slower).  The
+  // order is the same for both layouts of W, so both give the same bits.
+  int turn;
   int vt_base, n_vt_run;   // this launch's vocabulary tiles: vt_base .. vt_base + n_vt_run - 1
   // Group records, [M][rec_stride] each: the three largest logits of the group,
   // their positions in it (rec_i: 7 bits each, i1 | i2 << 7 | i3 << 14; any
@@ -461,7 +471,7 @@ constexpr int kDStage = 32;   // hidden channels per stage (64 bytes per row)
 
 __device__ __forceinline__ int dl_off(int r, int c) { return 64 * r + 16 * (c ^ ((r >> 2) & 3)); }
 
-template <int VB, int RB, int NBUF, int NW>
+template <int VB, int RB, int NBUF, int NW, bool TURN>
 __global__ __launch_bounds__(64 * NW) void lmhead_gemm_dlds_kernel(LmParams p) {
   static_assert(NBUF >= 3 && NBUF <= 5, "ring depth");
   static_assert(NW == 4 || NW == 8, "WV x WR waves");
@@ -523,6 +533,7 @@ __global__ __launch_bounds__(64 * NW) void lmhead_gemm_dlds_kernel(LmParams p) {
     }
   };
   set_src(vt, rt);
+  int rot = TURN ? 2 * (vt % (nst / 2)) : 0;     // the tile's first stage
   // Stage st goes to buffer st % NBUF.  Stages past the end reload the last
   // one into a free buffer, so that every wave has the same number of loads
   // in flight at every boundary.  dma(st, j0, j1): this wave's load blocks
@@ -532,7 +543,12 @@ __global__ __launch_bounds__(64 * NW) void lmhead_gemm_dlds_kernel(LmParams p) {
   const int wk = p.w_tiled ? 16 : 1;
   auto dma = [&](int st, int j0, int j1) {
     char* buf = s_ring + (st % NBUF) * SB;
-    const int k0 = min(st, nst - 1) * kDStage;
+    int s = min(st, nst - 1);
+    if constexpr (TURN) {
+      s += rot;
+      if (s >= nst) s -= nst;
+    }
+    const int k0 = s * kDStage;
     const bf16* wb = Wp + wk * k0;
     const bf16* hb = Ht + 16 * k0;
 #pragma unroll
@@ -659,6 +675,7 @@ __global__ __launch_bounds__(64 * NW) void lmhead_gemm_dlds_kernel(LmParams p) {
       asm volatile("" ::: "memory");
     }
     if (more) {
+      rot = TURN ? 2 * (vt % (nst / 2)) : 0;
       set_src(vt, rt);
 #pragma unroll
       for (int s0 = 0; s0 < NBUF - 1; ++s0) dma(s0, 0, PW);
@@ -682,12 +699,14 @@ __global__ __launch_bounds__(64 * NW) void lmhead_gemm_dlds_kernel(LmParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// Few rows (M <= 64, bf16): the same product as a stream of W.
+// Few rows (M <= 64, or 128 with a small vocabulary; bf16): the same product
+// as a stream of W.
 //
 // HBM bounds it (622 MB of W at V = 151936, Hd = 2048: 109 us at 5.7 TB/s), so
 // what counts is whole cache lines, bytes in flight and an even end.  A stage
 // is 64 channels, so that a row-major W is read in whole 128-byte lines too.
-// A workgroup owns WV record groups of 128 entries and 64 rows, two waves per
+// A workgroup owns WV record groups of 128 entries and 64 rows (further rows
+// in further row tiles, next to it on its XCD), two waves per
 // group (32 rows each), three stages in LDS; one or two workgroups share a
 // compute unit.  The grid is the tile count over whole rounds, so that every
 // workgroup walks the same number of tiles.  Hidden rows are read where they
@@ -725,7 +744,7 @@ __global__ __launch_bounds__(128 * WV, 1) void lmhead_gemm_stream_kernel(LmParam
   const char* Hp = reinterpret_cast<const char*>(p.hidden);
 
   unsigned src[PW];           // byte offsets from W (below 4 GiB) and from the hidden rows
-  auto set_src = [&](int vt_) {
+  auto set_src = [&](int vt_, int rt_) {
 #pragma unroll
     for (int j = 0; j < PW; ++j) {
       const int u = w + NW * j;
@@ -739,20 +758,13 @@ __global__ __launch_bounds__(128 * WV, 1) void lmhead_gemm_stream_kernel(LmParam
           src[j] = (unsigned)min(vt_ * NV + r, p.V - 1) * (unsigned)p.Hd * 2 + 16 * c;
         }
       } else {
-        src[j] = (unsigned)min(r, p.M - 1) * (unsigned)p.Hd * 2 + 16 * c;      // past M: never stored
+        src[j] = (unsigned)min(kSRows * rt_ + r, p.M - 1) * (unsigned)p.Hd * 2 + 16 * c;   // past M: never stored
       }
     }
   };
-  set_src(vt);
+  set_src(vt, rt);
   const int ws = p.w_tiled ? 2048 : 128;            // bytes a stage advances in W
-  // Rows a multiple of 4 KB apart lie on the same memory channel, and so do the
-  // lines a stage reads of all of them; workgroups that start together would
-  // ask the same channels.  Each pair of groups therefore starts its sum at a
-  // stage of its own (row-major W at Hd = 2048: 139 -> 120 us of call at M = 1;
-  // other Hd gain nothing or lose 5%).  The order depends on the group alone,
-  // so both layouts of W give the same bits.
-  const bool turn = p.Hd % 2048 == 0;
-  int rot = turn ? vt * WV / 2 % nst : 0;
+  int rot = p.turn ? vt * WV / 2 % nst : 0;         // the tile's first stage
   // Stages past the end reload the last one into a free buffer, so that every
   // wait has the same count.
   auto dma = [&](int st) {
@@ -800,23 +812,23 @@ __global__ __launch_bounds__(128 * WV, 1) void lmhead_gemm_stream_kernel(LmParam
       }
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // the reloads past the end
-    const int v_done = vt * NV + kGroup * wv;
+    const int v_done = vt * NV + kGroup * wv, m_done = kSRows * rt + 32 * wr;
     id += gridDim.x;
     const bool more = gemm_tile(p, id, vt, rt);
     if (more) {
       __builtin_amdgcn_s_barrier();   // every wave is done with the ring
       asm volatile("" ::: "memory");
-      set_src(vt);
-      rot = turn ? vt * WV / 2 % nst : 0;
+      set_src(vt, rt);
+      rot = p.turn ? vt * WV / 2 % nst : 0;
 #pragma unroll
       for (int s0 = 0; s0 < kSBuf - 1; ++s0) dma(s0);
     }
     if (v_done + kGroup <= p.V)
-      lm_epilogue<4, 1, true>(p, acc, v_done, 32 * wr, nullptr);
+      lm_epilogue<4, 1, true>(p, acc, v_done, m_done, nullptr);
     else if (v_done < p.V)
-      lm_epilogue<4, 1, false>(p, acc, v_done, 32 * wr, nullptr);
+      lm_epilogue<4, 1, false>(p, acc, v_done, m_done, nullptr);
     if (!more) break;
-    set_src(vt);   // again, rather than held in registers across the epilogue
+    set_src(vt, rt);   // again, rather than held in registers across the epilogue
     first = false;
   }
 }
@@ -1525,13 +1537,13 @@ int resident_slots(int (&cache)[64], const void* kernel, int threads) {
 
 // Launch of the persistent direct-to-LDS GEMM: as many workgroups as the
 // device holds at once, but no more than there are tile numbers.
-template <int VB, int RB, int NBUF, int NW>
+template <int VB, int RB, int NBUF, int NW, bool TURN = false>
 void launch_dlds(const LmParams& q, hipStream_t st) {
   static int slots[64] = {};
   const int n = resident_slots(
-      slots, reinterpret_cast<const void*>(&lmhead_gemm_dlds_kernel<VB, RB, NBUF, NW>), 64 * NW);
+      slots, reinterpret_cast<const void*>(&lmhead_gemm_dlds_kernel<VB, RB, NBUF, NW, TURN>), 64 * NW);
   const dim3 grid((unsigned)min((int)gemm_grid(q).x, n));
-  hipLaunchKernelGGL((lmhead_gemm_dlds_kernel<VB, RB, NBUF, NW>), grid, dim3(64 * NW), 0, st, q);
+  hipLaunchKernelGGL((lmhead_gemm_dlds_kernel<VB, RB, NBUF, NW, TURN>), grid, dim3(64 * NW), 0, st, q);
 }
 
 // Launch of the few-row stream: the groups over whole rounds of the device.
@@ -1540,9 +1552,10 @@ void launch_stream(LmParams q, hipStream_t st) {
   static int slots[64] = {};
   const int n = resident_slots(slots, reinterpret_cast<const void*>(&lmhead_gemm_stream_kernel<WV>), 128 * WV);
   q.n_vt_run = (q.n_groups + WV - 1) / WV;
-  q.n_rt = 1;
-  const int rounds = (q.n_vt_run + n - 1) / n;
-  const int grid = ((q.n_vt_run + rounds - 1) / rounds + 7) / 8 * 8;
+  q.n_rt = (q.M + kSRows - 1) / kSRows;
+  const int tiles = q.n_vt_run * q.n_rt;
+  const int rounds = (tiles + n - 1) / n;
+  const int grid = ((tiles + rounds - 1) / rounds + 7) / 8 * 8;
   hipLaunchKernelGGL(lmhead_gemm_stream_kernel<WV>, dim3((unsigned)grid), dim3(128 * WV), 0, st, q);
 }
 
@@ -1564,7 +1577,7 @@ void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
     // Two groups per workgroup where all the compute units get one, but for
     // the fewest rows (M = 1 120 us with one, 121 with two; M = 24 129 and
     // 125; M = 2, V = 32003 37 and 42).
-    if (p.n_groups <= 2 * device_cus() || p.M <= 8)
+    if (p.M <= kSRows && (p.n_groups <= 2 * device_cus() || p.M <= 8))
       launch_stream<1>(p, st);
     else
       launch_stream<2>(p, st);
@@ -1579,7 +1592,7 @@ void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
     // Each W tile is read by one compute unit alone: three rounds of four
     // waves (a third fewer LDS reads than eight half-group waves), no second
     // launch: M = 192 183 us against 206.
-    launch_dlds<4, 3, 4, 4>(p, st);
+    p.turn ? launch_dlds<4, 3, 4, 4, true>(p, st) : launch_dlds<4, 3, 4, 4>(p, st);
   } else if constexpr (RB >= 3) {
     // With one row tile (M <= 320): full-row tiles for as many whole rounds
     // of one tile per compute unit as the vocabulary fills; the vocabulary
@@ -1595,7 +1608,7 @@ void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
       q.vt_base = 0;
       q.n_vt_run = n_main;
       if constexpr (RB == 4)
-        launch_dlds<4, 2, 4, 8>(q, st);
+        p.turn ? launch_dlds<4, 2, 4, 8, true>(q, st) : launch_dlds<4, 2, 4, 8>(q, st);
       else
         launch_dlds<2, RB, 4, 8>(q, st);
     }
@@ -1603,10 +1616,10 @@ void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
       q.vt_base = n_main;
       q.n_vt_run = p.n_vt - n_main;
       q.n_rt = (p.M + 127) / 128;
-      launch_dlds<4, 1, 4, 8>(q, st);
+      p.turn ? launch_dlds<4, 1, 4, 8, true>(q, st) : launch_dlds<4, 1, 4, 8>(q, st);
     }
   } else if constexpr (RB == 2)
-    launch_dlds<4, 1, 4, 8>(p, st);
+    p.turn ? launch_dlds<4, 1, 4, 8, true>(p, st) : launch_dlds<4, 1, 4, 8>(p, st);
   else
     launch_dlds<4, RB, 4, 4>(p, st);
 }
@@ -1663,7 +1676,10 @@ LmPlan lm_plan(int M, int Hd, int V, int K, bool bf16) {
   // 320 / 281, M = 512 332 / 331 (256-row tiles either way).
   static constexpr int kRoundUs[6] = {0, 0, 42, 54, 62, 77};
   pl.rb = 1;
-  if (bf16 && M > 64) {
+  // Up to 128 rows stay with the few-row kernel (two row tiles) while one
+  // round holds their tiles of 256 entries (V = 32003: 44 us against 50, with
+  // a row-major W 64; V = 151936, tiled W: 164 against 140).
+  if (bf16 && M > 64 && (M > 128 || 2 * pl.n_vt > 256)) {
     long best = 0;
     for (int rb = 2; rb <= 5; ++rb) {
       const long n_rt = (M + 64L * rb - 1) / (64 * rb), n_vt = pl.n_vt;
@@ -1727,6 +1743,7 @@ hipError_t launch_lmhead(const LmLaunch& L, const LmPlan& pl, hipStream_t st) {
   if (L.M == 0) return hipSuccess;
   LmParams p = lm_params(L.hidden, L.W, L.M, L.Hd, L.V, L.K, pl, L.workspace);
   p.w_tiled = L.w_tiled ? 1 : 0;
+  p.turn = L.Hd % 2048 == 0 && L.M <= 256 ? 1 : 0;
   p.prop_tok = L.prop_tok;
   p.out_rows = L.out_rows;
   p.lse = L.lse;

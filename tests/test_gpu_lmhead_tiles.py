@@ -54,6 +54,22 @@ def test_row_tiles(M, last):
         assert torch.equal(g[key], t[key]), key
 
 
+@pytest.mark.parametrize("M", [128, 192, 256])
+def test_turned_sums(M):
+    """Hd = 2048: every vocabulary tile starts its sum at another channel, the
+    same one for both layouts of W."""
+    V, K = FULL + 130, 16
+    h, W, prop = _case(M, V, 2048, M)
+    p = torch.from_numpy(prop.astype(np.int32)).cuda()
+    g = ops.lmhead_logsoftmax_verify(h, W, p, K)
+    rows = np.arange(0, M, 13)
+    logits = oracle.logits_fp64(to_np(h)[rows], to_np(W))
+    parity.check_lmhead(g, oracle.lmhead_logsoftmax(None, None, prop[rows], K, logits=logits), logits, K, rows=rows)
+    t = ops.lmhead_logsoftmax_verify(h, ops.lmhead_pack_w(W), p, K)
+    for key in ("lse", "logp_prop", "argmax", "topk_idx", "topk_logp", "entropy"):
+        assert torch.equal(g[key], t[key]), key
+
+
 @pytest.mark.parametrize("M", [300, 384])
 def test_uniform_logits_join_halves(M):
     """W = 0: every logit ties, within and across the joined half groups."""
@@ -91,6 +107,8 @@ def test_draws_from_joined_records():
     (33, 65792 + 128, 128),   # two groups per workgroup, the last workgroup with one
     (64, 65792 + 129, 192),   # and with one group and an entry
     (64, 5003, 4096),
+    (65, 32003, 128),         # two row tiles
+    (128, 2048, 2048),
 ])
 def test_few_rows(M, V, Hd):
     h, W, prop = _case(M, V, Hd, M + V, dup=True)
