@@ -455,6 +455,59 @@ __global__ __launch_bounds__(256) void lmhead_gemm_kernel(LmParams p) {
   lm_epilogue_any<4, RB>(p, acc, vt, v0 + kGroup * wv, m0 + 32 * RB * wr, nullptr);
 }
 
+// fp32 with few tiles (a small vocabulary): one workgroup per record group and
+// 32 hidden rows, the channels split over its four waves, operands straight
+// from memory.  The kernel above gives 8 rows x 1024 entries (Hd = 256) to
+// eight workgroups, each wave with 256 channels of a 128 x 32 tile: 24 us, a
+// chain of 512 fp32 MFMAs.  A quarter of the channels per wave, summed through
+// LDS, takes 12.7.
+__global__ __launch_bounds__(256) void lmhead_gemm_f32_split_kernel(LmParams p) {
+  constexpr int NW = 4;
+  const int g = blockIdx.x, m0 = 32 * blockIdx.y;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = lane_id();
+  const int h = lane >> 5, rr = lane & 31;
+  __shared__ floatx16 s_acc[NW - 1][4][kWave];
+  const float* hr = reinterpret_cast<const float*>(p.hidden) + (size_t)min(m0 + rr, p.M - 1) * p.Hd + 4 * h;
+  const float* wr[4];
+#pragma unroll
+  for (int vb = 0; vb < 4; ++vb)   // rows past V: any valid row, masked later
+    wr[vb] = reinterpret_cast<const float*>(p.W) + (size_t)min(kGroup * g + 32 * vb + rr, p.V - 1) * p.Hd + 4 * h;
+  floatx16 acc[4][1];
+#pragma unroll
+  for (int vb = 0; vb < 4; ++vb)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[vb][0][e] = 0.f;
+  // Hd is a multiple of 64, so each wave's quarter of 16; lane half h takes
+  // channels c + 4 h .. c + 4 h + 3 of every 8, one per MFMA.
+  const int c1 = (w + 1) * (p.Hd / NW);
+#pragma unroll 2
+  for (int c = w * (p.Hd / NW); c < c1; c += 8) {
+    const floatx4 b = ld16<floatx4>(hr + c);
+    floatx4 a[4];
+#pragma unroll
+    for (int vb = 0; vb < 4; ++vb) a[vb] = ld16<floatx4>(wr[vb] + c);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int vb = 0; vb < 4; ++vb)
+        acc[vb][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[vb][e], b[e], acc[vb][0], 0, 0, 0);
+  }
+  if (w > 0)
+#pragma unroll
+    for (int vb = 0; vb < 4; ++vb) s_acc[w - 1][vb][lane] = acc[vb][0];
+  __syncthreads();
+  if (w > 0) return;
+#pragma unroll
+  for (int vb = 0; vb < 4; ++vb)
+#pragma unroll
+    for (int u = 0; u < NW - 1; ++u) acc[vb][0] += s_acc[u][vb][lane];
+  if (kGroup * (g + 1) <= p.V)
+    lm_epilogue<4, 1, true>(p, acc, kGroup * g, m0, nullptr);
+  else
+    lm_epilogue<4, 1, false>(p, acc, kGroup * g, m0, nullptr);
+}
+
 // ---------------------------------------------------------------------------
 // bf16 GEMM with direct-to-LDS operand loads (global_load_lds_dwordx4).
 //
@@ -966,40 +1019,42 @@ template <> struct Frag16<bf16> { typedef bf16x8 type; };
 template <> struct Frag16<float> { typedef floatx4 type; };
 
 // Exact logits of n vocabulary entries, vocab_of(e) for e < n (entries past V
-// give -inf), for the hidden row staged in s_hid (fp32).  A wave takes NB entries at a time and lane l covers channels
-// EPL l + 64 EPL i of each, so one load instruction reads 64 consecutive
-// 16-byte chunks of a W row and the loads of all NB entries (4 chunks each)
-// are in flight together; a shuffle reduction finishes each dot product.
-template <typename DT, int NB, typename VOCAB>   // NB: entries per wave and batch
+// give -inf), for the hidden row staged in s_hid (fp32).  LPE lanes share an
+// entry: lane l of them covers channels EPL (l + LPE i), so that eight lanes
+// read one 128-byte line of a W row and sixty-four a whole kilobyte; a wave
+// takes NB 64 / LPE entries at a time, with NP chunks of all of them in flight
+// per lane, and a lane reduction finishes each dot product.
+template <typename DT, int NB, int NP, int LPE, typename VOCAB>
 __device__ void recompute_entries(const LmParams& p, const float* s_hid, int n, VOCAB vocab_of,
                                   float* out_v, int* out_i) {
+  static_assert(LPE == 8 || LPE == 64, "lanes per entry");
   typedef typename Frag16<DT>::type frag;
   const DT* Wp = reinterpret_cast<const DT*>(p.W);
   constexpr int EPL = 16 / (int)sizeof(DT);
-  constexpr int NP = 4;                       // chunks per lane and entry in flight
+  constexpr int NE = kWave / LPE;             // entries side by side in the wave
   constexpr int NW = kMT / kWave;
-  const int lane = lane_id(), wv = threadIdx.x / kWave;
-  for (int e0 = wv * NB; e0 < n; e0 += NW * NB) {
+  const int lane = lane_id() % LPE, sub = lane_id() / LPE, wv = threadIdx.x / kWave;
+  for (int e0 = wv * NB * NE; e0 < n; e0 += NW * NB * NE) {
     float acc[NB];
     int vv[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      vv[b] = vocab_of(min(e0 + b, n - 1));
+      vv[b] = vocab_of(min(e0 + NE * b + sub, n - 1));
       acc[b] = 0.f;
     }
-    for (int c0 = 0; c0 < p.Hd; c0 += NP * kWave * EPL) {
+    for (int c0 = 0; c0 < p.Hd; c0 += NP * LPE * EPL) {
       frag w[NB][NP];
 #pragma unroll
       for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
           // out-of-range rows and channels load a valid chunk; it is masked below
-          const int c = min(c0 + EPL * (lane + kWave * i), p.Hd - EPL);
+          const int c = min(c0 + EPL * (lane + LPE * i), p.Hd - EPL);
           w[b][i] = ld16<frag>(Wp + w_off(p, min(vv[b], p.V - 1), c));
         }
 #pragma unroll
       for (int i = 0; i < NP; ++i) {
-        const int c = c0 + EPL * (lane + kWave * i);
+        const int c = c0 + EPL * (lane + LPE * i);
         if (c < p.Hd) {
           float hv[EPL];
 #pragma unroll
@@ -1014,23 +1069,33 @@ __device__ void recompute_entries(const LmParams& p, const float* s_hid, int n, 
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       float a = acc[b];
-      a = wave_sum(a);
-      if (lane == 0 && e0 + b < n) {
+      if constexpr (LPE == 64) {
+        a = wave_sum(a);
+      } else {
+        a += dpp_move<0x141>(a);   // row_half_mirror: within each eight lanes
+        a += dpp_move<0x4E>(a);    // quad_perm [2, 3, 0, 1]
+        a += dpp_move<0xB1>(a);    // quad_perm [1, 0, 3, 2]
+      }
+      const int e = e0 + NE * b + sub;
+      if (lane == 0 && e < n) {
         const bool ok = vv[b] < p.V;
-        out_v[e0 + b] = ok ? a : -INFINITY;
-        out_i[e0 + b] = ok ? vv[b] : 0x7fffffff;
+        out_v[e] = ok ? a : -INFINITY;
+        out_i[e] = ok ? vv[b] : 0x7fffffff;
       }
     }
   }
 }
 
-// The 128 logits of each listed group (split groups of the merge).
-template <typename DT, int NB = 4>
+// The 128 logits of each listed group (split groups of the merge): many rows
+// of W, short ones in the small models that need this, so eight lanes share a
+// row and a wave has 16 rows in flight (a wave per row, four at a time: 38 us
+// for the merge of 8 rows, V = 1024, Hd = 256 fp32; 25 so).
+template <typename DT>
 __device__ void recompute_logits(const LmParams& p, const float* s_hid, const int* s_split, int ns,
                                  float* out_v, int* out_i) {
-  recompute_entries<DT, NB>(p, s_hid, ns * kGroup,
-                            [&](int e) { return s_split[e / kGroup] * kGroup + e % kGroup; },
-                            out_v, out_i);
+  recompute_entries<DT, 2, 8, 8>(p, s_hid, ns * kGroup,
+                                 [&](int e) { return s_split[e / kGroup] * kGroup + e % kGroup; },
+                                 out_v, out_i);
 }
 
 template <typename DT>
@@ -1493,7 +1558,7 @@ __global__ __launch_bounds__(kMT) void sample_kernel(LmParams p, SampleParams s)
   const int v0 = gsel * kGroup + 32 * qsel;
   // exact logits of the quarter's 32 entries (one batch: 8 per wave), then
   // the draw inside it at the same fraction of its mass
-  recompute_entries<DT, 8>(p, s_hid, 32, [&](int e) { return v0 + e; }, s_cv, s_ci);
+  recompute_entries<DT, 8, 4, 64>(p, s_hid, 32, [&](int e) { return v0 + e; }, s_cv, s_ci);
   __syncthreads();
   if (tid < kWave) {
     const float a = tid < 32 ? s_cv[tid] : -INFINITY;
@@ -1627,6 +1692,11 @@ void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
 template <int RB>
 void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, float) {
   trace_mark(st);   // no hidden copy for fp32: an empty interval
+  // Few tiles leave most compute units idle: split them further.
+  if (p.n_vt * p.n_rt <= 64) {
+    hipLaunchKernelGGL(lmhead_gemm_f32_split_kernel, dim3(p.n_groups, (p.M + 31) / 32), dim3(256), 0, st, p);
+    return;
+  }
   hipLaunchKernelGGL((lmhead_gemm_kernel<float, RB>), grid, dim3(256), 0, st, p);
 }
 
@@ -1783,7 +1853,7 @@ __global__ __launch_bounds__(kMT) void logp_gather_kernel(LmParams p, const floa
   __syncthreads();
   const int32_t* ir = idx + (size_t)m * n;
   // indices outside [0, V) read as V: recompute_entries gives them -inf
-  recompute_entries<DT, 4>(p, s_hid, n, [&](int e) {
+  recompute_entries<DT, 4, 4, 64>(p, s_hid, n, [&](int e) {
     const int v = ir[e];
     return (v < 0 || v >= p.V) ? p.V : v;
   }, s_v, s_i);

@@ -126,3 +126,39 @@ def test_few_rows(M, V, Hd):
     for key in ("lse", "logp_prop", "argmax", "topk_idx", "topk_logp", "entropy"):
         assert torch.equal(g[key], t[key]), key
     parity.check_lmhead(o, oracle.lmhead_logsoftmax(None, None, prop, K, logits=logits), logits, K)
+
+
+@pytest.mark.parametrize("M,V,Hd", [(1, 130, 64), (33, 4000, 192), (70, 20000, 64)])
+def test_fp32_split_and_staged(M, V, Hd):
+    """fp32: few tiles split the channels over the waves; V = 20000 with two
+    row tiles stages them."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(V)
+    h = torch.randn(M, Hd, generator=gen, device="cuda")
+    W = torch.randn(V, Hd, generator=gen, device="cuda") * 0.1
+    prop = np.random.default_rng(V).integers(0, V, size=M)
+    g = ops.lmhead_logsoftmax_verify(h, W, torch.from_numpy(prop.astype(np.int32)).cuda(), 16)
+    logits = oracle.logits_fp64(to_np(h), to_np(W))
+    parity.check_lmhead(g, oracle.lmhead_logsoftmax(None, None, prop, 16, logits=logits), logits, 16)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("Hd", [64, 320, 4096])
+def test_recomputed_groups(Hd, dtype):
+    """Seven of the top 16 in each of two groups: their 128 logits are
+    recomputed, at hidden sizes below, between and at multiples of a pass."""
+    V, K = 3000, 16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(Hd)
+    h = torch.randn(3, Hd, generator=gen, device="cuda")
+    W = torch.randn(V, Hd, generator=gen, device="cuda") / Hd ** 0.5
+    top = [*range(200, 207), *range(2950, 2957)]
+    for r, v in enumerate(top):
+        W[v] += h.mean(0) * (8 + 0.25 * r) / Hd
+    h, W = h.to(dtype), W.to(dtype)
+    prop = np.array([0, 203, 2999])
+    g = ops.lmhead_logsoftmax_verify(h, W, torch.from_numpy(prop.astype(np.int32)).cuda(), K)
+    logits = oracle.logits_fp64(to_np(h), to_np(W))
+    per_group = [max(np.bincount(np.argsort(-l)[:K] // 128)) for l in logits]
+    assert min(per_group) >= 4, per_group
+    parity.check_lmhead(g, oracle.lmhead_logsoftmax(None, None, prop, K, logits=logits), logits, K)
