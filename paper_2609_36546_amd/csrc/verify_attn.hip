@@ -82,14 +82,14 @@ struct AttnParams {
   int page_size, log2ps, num_pages;
   int chunk, sub;     // keys per workgroup chunk / per wave
   int max_chunks, n_qg, n_seq;
-  int max_q;          // bound of the handled windows' rows
-  int al16;           // the window and cache arrays start on 16-byte boundaries
   float scale_log2;   // softmax scale * log2(e)
   int32_t* sk_start;  // stream-K: first block of every item (written by the attention kernel)
   int32_t* sk_ne;     // stream-K: non-empty items before every item (written with sk_start)
   int sk_grid;        // stream-K: persistent workgroups
   int item_rows;      // stream-K: packed query rows per item (64, or 128 with two tiles per wave)
   int sk_first;       // stream-K: workgroups dispatched first on their CU (the CU count)
+  int max_q;          // bound of the handled windows' rows
+  int al16;           // the window and cache arrays start on 16-byte boundaries
 };
 
 template <typename DT, int D> struct Frags;
@@ -634,6 +634,18 @@ constexpr int kSkBuf = 3;              // ring depth (units)
 constexpr int kSkUnit = 16384;         // bytes per unit
 constexpr int kSkMeta = 7680;          // ints of LDS for item tables, sequence data, page ids, unit records
 constexpr int kSkGrid = 512;           // persistent workgroups: 2 per CU
+// Workgroups that share the B blocks of NE non-empty items.  A call with few
+// blocks is bound by latency: the blocks of a workgroup one after the other,
+// then the combine's walk over an item's pieces.  The longer the items, the
+// more blocks a workgroup takes: 3 to 8 by the mean item, up to the full grid.
+// Against one block per workgroup, us per call: 1 student row over 1500 keys
+// 18.7 -> 14.9, 3 windows of 8 teacher rows to 2912 keys 28.2 -> 19.1, one of
+// 16 student rows over 9237 keys 29.5 -> 25.1.
+__host__ __device__ inline int sk_workgroups(int grid, int B, int NE) {
+  if (B >= 8 * grid) return grid;   // without the divisions
+  const int w = B < 24 * NE ? (B + 2) / 3 : B < 40 * NE ? (B + 3) / 4 : B < 150 * NE ? (B + 4) / 5 : (B + 7) / 8;
+  return w < grid ? w : grid;
+}
 
 __device__ __forceinline__ int kpiece_unit(int slot, int q) {
   return 4 * slot + (q ^ (((slot >> 1) & 1) | ((slot >> 2) & 2)));
@@ -857,7 +869,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
     // Share w: the blocks whose cost start lies in [y_lo, y_hi), in quarter
     // blocks (sk_item_cost), the spans weighted by XCD and CU slot (kSkSpan).
     constexpr int c4 = sk_item_cost(QT);
-    W = min((int)gridDim.x, B_tot);
+    W = sk_workgroups((int)gridDim.x, B_tot, NE);
     const int C = 4 * B_tot + c4 * NE;
     const SkSpan sp = sk_spans(B_tot, W, a.sk_first);
     const long SW = sk_span_prefix(W, sp);
@@ -1348,7 +1360,7 @@ __global__ __launch_bounds__(256) void attn_combine_sk_kernel(AttnParams a) {
   const int kb = a.cu_q[b + 1] - r0;
   if (s1 <= s0) return;
   const int NE = a.sk_ne[n_it], ne = a.sk_ne[it];
-  const int W = min(a.sk_grid, B_tot);
+  const int W = sk_workgroups(a.sk_grid, B_tot, NE);
   // Workgroup whose share holds block x: the last w whose span starts, at
   // C S(w) / S(W), at or below the block's cost start 4 x + c4 (ne + 1) (the
   // attention kernel's split; S the weighted span prefix).
@@ -1572,7 +1584,9 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
     pl.sk_grid = (int)std::max(0L, std::min((long)kSkGrid, held & ~1L));
   }
   const long wden = 4L * std::max(pl.sk_grid, 1) * wmin;
-  const long share = std::max((n_it * (4 * maxblk + c4) * wmax + wden - 1) / wden, (c4 + 3) / 4 + 1) + 2;
+  // Below the full grid (sk_workgroups) a share averages m blocks and m NE / B
+  // item starts: at most 3 + 3 c4 / 4 blocks.
+  const long share = std::max((n_it * (4 * maxblk + c4) * wmax + wden - 1) / wden, c4 + 5) + 2;
   pl.sk = D == 128 && pl.sk_grid >= 128 && n_it * (4 * maxblk + c4) < (1L << 31) &&
           2 * (n_it + 1) + 4L * n_seq + 3 * share + pl.sk_qt * n_it <= kSkMeta;
   // Tiles without a split (verify_attn_tile_kernel), or shares of all items
