@@ -1190,8 +1190,8 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
 // combine, no tables.  Four waves of 16 QT packed rows each share the 32-key
 // units of an LDS ring laid out as below.  QT = 2 at 159 registers and a ring
 // of three units keeps three workgroups on a CU; QT = 3 (221 registers, two
-// workgroups) took 96 us where this takes 82 (eight prompts of 512-1024
-// tokens, teacher heads: 0.45 PFLOP/s; the register kernel took 484), and
+// workgroups) took 96 us where this takes 88 (eight prompts of 512-1024
+// tokens, teacher heads: 0.46 PFLOP/s; the register kernel took 484), and
 // QT = 4 spills.  What bounds it is the chain within a unit (scores, row
 // maximum, exponentials, second product), of which three waves per SIMD hide
 // a part.  Rows of a wave are neighbours: near the causal edge a wave skips
@@ -1602,7 +1602,7 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
   //   teacher tokens: 41 / 92; 4 windows of 256 rows, contexts to 4096: 119 / 109.
   // More items than the stream-K tables hold, with more than 64 rows each,
   // fill the chip as tiles at any length (eight prompts of 512-1024 tokens:
-  // register kernel 484 us, tiles 82 us).
+  // register kernel 484 us, tiles 88 us).
   const double fixed = 9 + 0.03 * max_q;
   if (D == 128 && (0.75 * maxblk <= fixed + 0.002 * std::min(n_it, 256L) * maxblk ||
                    (!pl.sk && n_it >= kSkGrid && rows > kRows)))
