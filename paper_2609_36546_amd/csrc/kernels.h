@@ -40,6 +40,7 @@ struct AttnPlan {
   int chunk;           // keys per workgroup
   int max_chunks;      // chunk slots per group (padded to a multiple of 8)
   int tile;            // unsplit tiles of 64 * tile query rows, 0: not taken (bf16, D = 128)
+  int max_mask;        // tiles: the key blocks that take their own maximum as reference
   int sk;              // persistent stream-K kernel (bf16, D = 128)
   int sk_grid;         // stream-K: persistent workgroups
   int sk_qt;           // stream-K: 16-row tiles per wave (1: 64-row items, 2: 128-row items)

@@ -51,6 +51,7 @@
 // the block arithmetic (attend_block) and the pool layouts.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -89,6 +90,7 @@ struct AttnParams {
   int item_rows;      // stream-K: packed query rows per item (64, or 128 with two tiles per wave)
   int sk_first;       // stream-K: workgroups dispatched first on their CU (the CU count)
   int max_q;          // bound of the handled windows' rows
+  int max_mask;       // tiles: key block n takes its own maximum as reference where (n - 1) & max_mask is 0
   int al16;           // the window and cache arrays start on 16-byte boundaries
 };
 
@@ -211,12 +213,30 @@ template <int D, int QT> struct RegQT {
   __device__ __forceinline__ bf16x8 get(int t, int ks) const { return q[t][ks]; }
 };
 
+// What a row's probabilities are taken against before they are rounded to bf16.
+// LazyMax: the running maximum, moved only when outgrown by kRescaleSlack.
+struct LazyMax {};
+// BlockMax: with `slack` at -inf the block's own maximum (but not below the
+// row's peak less kPeakSpan, which keeps the sums finite), so that the block's
+// heaviest key is exact in bf16; with kRescaleSlack as LazyMax.  The fewer keys
+// share a reference, the smaller the error: outputs of one row over 1500 random
+// keys are 0.00201 off their 64-bit values (rms, relative) with a reference for
+// every 32 keys, 0.00228 with one for 160 (0.0017 is the outputs' own rounding).
+constexpr float kPeakSpan = 24.f;   // log2 units
+template <int QT> struct BlockMax {
+  float slack;
+  float peak[QT];
+  __device__ __forceinline__ void reset() {
+#pragma unroll
+    for (int t = 0; t < QT; ++t) peak[t] = -INFINITY;
+  }
+};
 
-template <typename DT, int D, int QT, bool TAIL, class QS, class FS>
+template <typename DT, int D, int QT, bool TAIL, class QS, class FS, class REF = LazyMax>
 __device__ __forceinline__ void attend_block(const AttnParams& a, const FS& f,
                                              const QS& qs, const int (&qlimit)[QT],
                                              int t0, floatx4 (&acc)[QT][D / 16],
-                                             float (&m_run)[QT], float (&l_run)[QT]) {
+                                             float (&m_run)[QT], float (&l_run)[QT], REF&& ref = REF{}) {
   const int lane = lane_id();
   const int j = lane >> 4, c16 = lane & 15;
   floatx4 s[QT][2];
@@ -265,7 +285,13 @@ __device__ __forceinline__ void attend_block(const AttnParams& a, const FS& f,
   for (int t = 0; t < QT; ++t) {
     const float bx = bm[t] * c;
     const float m_old = m_run[t];
-    const float m_new = (bx > m_old + kRescaleSlack || m_old == -INFINITY) ? fmaxf(bx, m_old) : m_old;
+    float m_new;
+    if constexpr (std::is_same_v<std::decay_t<REF>, LazyMax>) {
+      m_new = (bx > m_old + kRescaleSlack || m_old == -INFINITY) ? fmaxf(bx, m_old) : m_old;
+    } else {
+      ref.peak[t] = fmaxf(ref.peak[t], bx);
+      m_new = (bx > m_old + ref.slack || m_old == -INFINITY) ? fmaxf(bx, ref.peak[t] - kPeakSpan) : m_old;
+    }
     m_use[t] = (m_new == -INFINITY) ? 0.f : m_new;
     rescale |= m_new != m_old;
     bm[t] = m_old;          // keep the old running max for the rescale factor
@@ -1059,6 +1085,10 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
   // Compute side.  The units come as items: QT query units, then the item's
   // key/value units up to the one that ends its piece.  Tile tt of this wave
   // holds the item's rows 64 tt + 16 t .. 64 tt + 16 t + 15.
+  // Few blocks are dealt several to a workgroup (sk_workgroups), and the larger
+  // pages' shares are longer than the register kernel's: each block takes its
+  // own maximum there (at most 0.5 us of a call).
+  const bool block_max = PS != 16 || W < (int)gridDim.x;
   int c_rec = uni(s_uq[0]);
   int n = 0;
   // Unit n of this wave's loads has landed (the next one may still be in
@@ -1108,6 +1138,8 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
     }
     floatx4 acc[QT][D / 16];
     float m_run[QT], l_run[QT];
+    BlockMax<QT> ref{block_max ? -INFINITY : kRescaleSlack};
+    ref.reset();
 #pragma unroll
     for (int tt = 0; tt < QT; ++tt) {
       m_run[tt] = -INFINITY;
@@ -1128,7 +1160,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
       const char* buf = next_unit(rec);
       if (has_rows[0]) {
         const LdsFrags<false, kSkVStep<PS>> f{buf, k_off[0], k_off[1], v_off0, 0, 0};
-        attend_block<bf16, D, QT, false>(a, f, qf, qlimit, t0, acc, m_run, l_run);
+        attend_block<bf16, D, QT, false>(a, f, qf, qlimit, t0, acc, m_run, l_run, ref);
       }
       if (rec & 2) { ended = true; break; }
     }
@@ -1137,7 +1169,7 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
       const int t0 = kBlk * ((rec >> 2) - x0);
       if (has_rows[0]) {
         const LdsFrags<true, kSkVStep<PS>> f{buf, k_off[0], k_off[1], v_off0, t0 + 8 * j, it.n_keys};
-        attend_block<bf16, D, QT, true>(a, f, qf, qlimit, t0, acc, m_run, l_run);
+        attend_block<bf16, D, QT, true>(a, f, qf, qlimit, t0, acc, m_run, l_run, ref);
       }
       ended = rec & 2;
     }
@@ -1258,6 +1290,8 @@ __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) 
 
   floatx4 acc[QT][D / 16];
   float m_run[QT], l_run[QT];
+  BlockMax<QT> ref{-INFINITY};
+  ref.reset();
 #pragma unroll
   for (int tt = 0; tt < QT; ++tt) {
     m_run[tt] = -INFINITY;
@@ -1308,14 +1342,16 @@ __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) 
       const char* buf = next_unit(n);
       if (has_rows) {
         const LdsFrags<false, kSkVStep<PS>> f{buf, k_off[0], k_off[1], v_off0, 0, 0};
-        attend_block<bf16, D, QT, false>(a, f, qf, qlimit, kBlk * n, acc, m_run, l_run);
+        ref.slack = ((n - 1) & a.max_mask) ? kRescaleSlack : -INFINITY;
+        attend_block<bf16, D, QT, false>(a, f, qf, qlimit, kBlk * n, acc, m_run, l_run, ref);
       }
     }
     for (int n = max(n0, f1); n < n1; ++n) {
       const char* buf = next_unit(n);
       if (n < n_mine) {
         const LdsFrags<true, kSkVStep<PS>> f{buf, k_off[0], k_off[1], v_off0, kBlk * n + 8 * j, n_keys};
-        attend_block<bf16, D, QT, true>(a, f, qf, qlimit, kBlk * n, acc, m_run, l_run);
+        ref.slack = ((n - 1) & a.max_mask) ? kRescaleSlack : -INFINITY;
+        attend_block<bf16, D, QT, true>(a, f, qf, qlimit, kBlk * n, acc, m_run, l_run, ref);
       }
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // reloads past the batch's end
@@ -1607,6 +1643,16 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
   if (D == 128 && (0.75 * maxblk <= fixed + 0.002 * std::min(n_it, 256L) * maxblk ||
                    (!pl.sk && n_it >= kSkGrid && rows > kRows)))
     pl.tile = pl.sk_qt;
+  // How many of a tile's key blocks take their own maximum as reference
+  // (BlockMax): about as many as one in every workgroup's share when the blocks
+  // are split over the chip, so that a tile is no further from 64 bits than the
+  // split.  Error (rms, relative, split / tile with no block / as chosen): 4
+  // windows of 8 teacher rows, contexts to 1000 (all blocks) 0.00208 / 0.00226 /
+  // 0.00203; a prompt of 1024 teacher tokens (every fourth) 0.000794 / 0.000799 /
+  // 0.000762; eight of 512-1024 (every eighth) 0.000923 / 0.000924 / 0.000894.
+  // All blocks would cost the eight prompts 7.2 us of 92, every eighth 1.2.
+  const long blocks = n_it * maxblk;
+  pl.max_mask = blocks <= 2048 ? 0 : blocks <= 4096 ? 1 : blocks <= 8192 ? 3 : 7;
   if (pl.sk) {
     const size_t sk_slots = (size_t)n_it + pl.sk_grid;
     pl.sk_o_bytes = sk_slots * sk_rows * D * sizeof(float);
@@ -1691,6 +1737,7 @@ hipError_t launch_verify_attn(const AttnLaunch& L, const AttnPlan& pl, hipStream
   p.n_qg = pl.n_qg;
   p.n_seq = L.n_seq;
   p.max_q = L.max_q;
+  p.max_mask = pl.max_mask;
   const uintptr_t bases = reinterpret_cast<uintptr_t>(L.q) | reinterpret_cast<uintptr_t>(L.k_new) |
                           reinterpret_cast<uintptr_t>(L.v_new) | reinterpret_cast<uintptr_t>(L.k_cache) |
                           reinterpret_cast<uintptr_t>(L.v_cache);

@@ -97,3 +97,53 @@ def test_stream_k_with_a_wide_page_table(Hq, Hkv, ks, lo, hi, B, keys, ps):
     by the table's width, so these batches take the stream-K split."""
     b = _batch(Hq, Hkv, ks, lo, hi, ps, seed=64, B=B)
     _check(b, page_table=_wide(b.models[0], keys // ps))
+
+
+def _block_rounded(q, K, V, limits, scale):
+    """Attention rows in 64 bits but for the probabilities, rounded to bf16
+    against the maximum of their 32-key block, and the outputs, to bf16; and
+    the rows unrounded.  q [R, D], K / V [N, D], limits [R] visible keys."""
+    s = (q @ K.t()) * scale / np.log(2.0)
+    s = s.masked_fill(torch.arange(K.shape[0])[None, :] >= limits[:, None], -torch.inf)
+    exact = torch.softmax(s * np.log(2.0), 1) @ V
+    pad = -s.shape[1] % 32
+    b = torch.nn.functional.pad(s, (0, pad), value=-torch.inf).view(len(q), -1, 32)
+    m = b.amax(2, keepdim=True)
+    p = torch.where(torch.isinf(b), torch.zeros_like(b), torch.exp2(b - m))
+    w = torch.exp2(m - m.amax(1, keepdim=True))
+    low = (p.to(torch.bfloat16).double() * w).flatten(1)[:, : s.shape[1]]
+    return (low @ V / (p * w).sum((1, 2))[:, None]).to(torch.bfloat16).double(), exact
+
+
+@pytest.mark.parametrize("Hq,Hkv,ks,lo,hi,ps,B", [
+    (16, 8, (1,), 1500, 1500, 16, 1),        # stream-K, fewer workgroups than the grid: five blocks each
+    (32, 4, (8,), 700, 2900, 16, 2),         # the same, three blocks each
+    (32, 4, (5,), 1500, 2500, 64, 12),       # stream-K over 64-slot pages
+    (32, 4, (8,), 150, 900, 16, 3),          # tiles: few windows, short contexts
+    (16, 8, (200,), 0, 0, 16, 1),            # tiles: a short prompt
+])
+def test_rounding_of_probabilities(Hq, Hkv, ks, lo, hi, ps, B):
+    """Calls of few key blocks round each block's probabilities against the
+    block's own maximum: the error against 64 bits is that of a model of this
+    rounding (2% apart at most: the hardware's exp2 and fp32 scores turn a few
+    roundings over), where one maximum for a whole piece or row gives 5 to 15%
+    more."""
+    b = _batch(Hq, Hkv, ks, lo, hi, ps, seed=70 + B, B=B)
+    mdl = b.models[0]
+    out, kc, vc = parity.run_gpu_attention(mdl, b, seq_ids=mdl.seq_ids)
+    G, D = Hq // Hkv, 128
+    table = mdl.page_table.cpu().long()
+    kc, vc, q, out = kc.cpu(), vc.cpu(), mdl.q.cpu(), out.cpu().double()
+    got = want = 0.0
+    for i in range(B):
+        L, r0, r1 = int(b.ctx_lens[i]), int(b.cu_q[i]), int(b.cu_q[i + 1])
+        pos = torch.arange(L + r1 - r0)
+        K = kc[table[i, pos // ps], :, :, pos % ps].reshape(len(pos), Hkv, D).double()
+        V = vc[table[i, pos // ps], :, :, pos % ps].double()
+        limits = L + 1 + torch.arange(r1 - r0)
+        for h in range(Hq):
+            low, exact = _block_rounded(q[r0:r1, h].double(), K[:, h // G], V[:, h // G], limits, D ** -0.5)
+            got += float(((out[r0:r1, h] - exact) ** 2).sum())
+            want += float(((low - exact) ** 2).sum())
+    print(f"[rounding] error against the model's: {(got / want) ** 0.5:.4f}", flush=True)
+    assert (got / want) ** 0.5 < 1.02
