@@ -39,7 +39,10 @@ struct AttnPlan {
   int sub;             // keys per wave
   int chunk;           // keys per workgroup
   int max_chunks;      // chunk slots per group (padded to a multiple of 8)
-  int tile;            // unsplit tiles of 64 * tile query rows, 0: not taken (bf16, D = 128)
+  int tile;            // tiles of 64 * tile query rows, 0: not taken (bf16, D = 128)
+  int tile_units;      // tiles: units per (sequence, KV head) at most
+  int tile_split;      // tiles: some may be cut by their keys (a combine follows)
+  int tile_walk;       // tiles: key blocks per piece at least
   int max_mask;        // tiles: the key blocks that take their own maximum as reference
   int sk;              // persistent stream-K kernel (bf16, D = 128)
   int sk_grid;         // stream-K: persistent workgroups

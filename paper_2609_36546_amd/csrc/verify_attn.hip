@@ -40,15 +40,16 @@
 // log-sum-exp form, unless the sequence fits in one chunk (then the
 // workgroup writes the output itself).
 //
-// bf16 D = 128 heads (every bf16 workload), when the kernel's LDS tables fit, take a second kernel, verify_attn_sk_kernel below:
-// persistent workgroups whose waves own one or two 16-row tiles (items of 64
+// bf16 D = 128 heads (every bf16 workload), when the kernel's LDS tables fit,
+// take a second kernel, verify_attn_sk_kernel below: persistent workgroups whose waves own one or two 16-row tiles (items of 64
 // or 128 rows of one (sequence, KV head)), keys and values streamed through
 // an LDS ring with direct-to-LDS loads, and the key blocks of all items split
 // evenly between workgroups (stream-K); items split between workgroups are
 // merged by attn_combine_sk_kernel.  bf16 D = 128 heads with long windows or
-// short contexts take a third, verify_attn_tile_kernel: unsplit tiles of query
-// rows that walk all their keys (attn_plan has the rule).  The kernels share
-// the block arithmetic (attend_block) and the pool layouts.
+// short contexts take a third, verify_attn_tile_kernel: tiles of query rows that
+// walk their keys, long walks cut into pieces by the window's own rows
+// (attn_plan has the rule).  The kernels share the block arithmetic
+// (attend_block) and the pool layouts.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -91,6 +92,7 @@ struct AttnParams {
   int sk_first;       // stream-K: workgroups dispatched first on their CU (the CU count)
   int max_q;          // bound of the handled windows' rows
   int max_mask;       // tiles: key block n takes its own maximum as reference where (n - 1) & max_mask is 0
+  int tile_walk;      // tiles: key blocks per piece at least
   int al16;           // the window and cache arrays start on 16-byte boundaries
 };
 
@@ -1218,8 +1220,9 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
 // With hundreds of window rows per (sequence, KV head) the work is no longer
 // the stream of keys but the two products and the softmax between them, and
 // with short contexts it is the fixed cost of a split; either way a workgroup
-// takes 64 QT query rows and walks all their keys: no split, no partials, no
-// combine, no tables.  Four waves of 16 QT packed rows each share the 32-key
+// takes 64 QT query rows and walks their keys: no tables, and no split, no
+// partials and no combine while the keys are few for the window's rows
+// (tile_split).  Four waves of 16 QT packed rows each share the 32-key
 // units of an LDS ring laid out as below.  QT = 2 at 159 registers and a ring
 // of three units keeps three workgroups on a CU; QT = 3 (221 registers, two
 // workgroups) took 96 us where this takes 88 (eight prompts of 512-1024
@@ -1228,12 +1231,71 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
 // maximum, exponentials, second product), of which three waves per SIMD hide
 // a part.  Rows of a wave are neighbours: near the causal edge a wave skips
 // the units past its last row.
+//
+// The host knows bounds, not windows: one long window, or a generous max_q,
+// brings its whole batch here, rows with long contexts among it.  A tile that
+// walked all the keys of such a row would take 0.75 us for each block, one
+// workgroup alone: 16 one-row windows to 32K tokens under max_q = 512 took 780
+// us so, a 512-token prompt beside 15 of them 785 (the register kernel 218 and
+// 585).  So every window cuts its keys by its own number of tiles: a single
+// tile takes pieces of 16 blocks, or up to 48 where many (sequence, head)s
+// share the chip, and a window of n tiles pieces of 16 n, since it brings n
+// workgroups for each piece and n 64-row partials to merge.  Now 188 and 189
+// us; four one-row windows to 5000 tokens under max_q = 1024 126 -> 29.5
+// (stream-K 28.4).
 // The grid has (sequence, head) fastest, padded to a multiple of 8, so that
 // all tiles of one (sequence, head) share an XCD's L2 (their keys come from
 // HBM once); the last tiles, which see the most keys, are dealt first.
 // ---------------------------------------------------------------------------
 constexpr int kTileBuf = 3;          // ring depth (units)
 constexpr int kTileBatch = 256;      // units whose page ids are held at a time
+constexpr int kTileWhole = 48;       // key blocks that any tile walks unsplit (a combine takes 5 us)
+constexpr int kTilePer = 16;         // blocks per piece at least, for each tile of the window
+
+// Tiles of a window of `rows` packed rows over nbk key blocks, and the pieces
+// that the keys are cut into: nt tiles, nc pieces of cb blocks each (those past
+// a tile's own last key are not run; a tile whose keys lie in the first piece
+// writes its output itself).  walk: blocks per piece at least; slots: 64-row
+// partials that the workspace holds for one (sequence, KV head).  64-row tiles
+// are taken for fewer blocks than kTileWhole only.
+struct TileSplit {
+  int nt, nc, cb;
+};
+__device__ __forceinline__ TileSplit tile_split(int rows, int nbk, int tile_rows, int walk, int slots) {
+  TileSplit s{(rows + tile_rows - 1) / tile_rows, 1, nbk};
+  if (tile_rows == 128 && nbk > kTileWhole) {
+    const int cb = max(s.nt * kTilePer, walk);
+    s.nc = min((nbk + cb - 1) / cb, slots / ((rows + kRows - 1) / kRows));
+    s.cb = (nbk + s.nc - 1) / s.nc;
+    s.nc = (nbk + s.cb - 1) / s.cb;
+  }
+  return s;
+}
+// The most units that a window of at most `tiles` tiles and maxblk blocks can have.
+inline long tile_units(long tiles, long maxblk) {
+  return maxblk <= kTileWhole ? tiles : tiles + (maxblk + kTilePer - 1) / kTilePer;
+}
+
+// The tiles of one sequence's window in one KV head, as the tile kernel and
+// its combine see them.
+struct TileWindow {
+  int L, r0, rows, maxblk;
+  TileSplit s;
+  __device__ __forceinline__ TileWindow(const AttnParams& a, int b, int tile_rows) {
+    L = max(a.ctx_lens[b], 0);
+    r0 = a.cu_q[b];
+    const int k = a.cu_q[b + 1] - r0;
+    rows = min(k * a.G, a.n_qg * kRows);
+    maxblk = (a.max_pages * a.page_size + kBlk - 1) / kBlk;
+    if (rows > 0) s = tile_split(rows, min((L + k + kBlk - 1) / kBlk, maxblk), tile_rows, a.tile_walk,
+                                 a.n_qg * a.max_chunks);
+  }
+  // Keys that the rows up to pr_last see, and their blocks.
+  __device__ __forceinline__ int keys(const AttnParams& a, int pr_last) const { return L + pr_last / a.G + 1; }
+  __device__ __forceinline__ int blocks(const AttnParams& a, int pr_last) const {
+    return min((keys(a, pr_last) + kBlk - 1) / kBlk, maxblk);
+  }
+};
 
 template <int PS, int QT>
 __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) {
@@ -1243,16 +1305,20 @@ __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) 
   if ((int)blockIdx.x >= n_sg) return;
   const int slot = blockIdx.x / a.Hkv, g = blockIdx.x % a.Hkv;
   const int b = a.seq_ids ? a.seq_ids[slot] : slot;
-  const int L = max(a.ctx_lens[b], 0);
-  const int r0 = a.cu_q[b];
-  const int rows_total = (a.cu_q[b + 1] - r0) * a.G;
-  // tiles from the last one that this window may have (max_q) down
-  const int pr0 = (int)(gridDim.y - 1 - blockIdx.y) * 64 * QT;
-  if (pr0 >= rows_total) return;
-  const int pr_last = min(rows_total, pr0 + 64 * QT) - 1;
-  const int maxblk = (a.max_pages * PS + kBlk - 1) / kBlk;
-  const int n_keys = L + pr_last / a.G + 1;
-  const int nb = min((n_keys + kBlk - 1) / kBlk, maxblk);
+  const TileWindow win(a, b, 64 * QT);
+  if (win.rows <= 0) return;
+  const int L = win.L, r0 = win.r0;
+  // units from the last one that a window of the call may have down
+  const int unit = gridDim.y - 1 - blockIdx.y;
+  const int tile = win.s.nc == 1 ? unit : unit / win.s.nc, piece = unit - tile * win.s.nc;
+  if (tile >= win.s.nt) return;
+  const int pr0 = tile * 64 * QT;
+  const int pr_last = min(win.rows, pr0 + 64 * QT) - 1;
+  const int n_keys = win.keys(a, pr_last);
+  const int nb_all = win.blocks(a, pr_last);
+  const int nb0 = piece * win.s.cb, nb = min(nb0 + win.s.cb, nb_all);   // this unit's key blocks
+  if (nb0 >= nb) return;
+  const bool whole = nb_all <= win.s.cb;
   const int tid = threadIdx.x;
   const int t = uni(tid / kWave);
   const int lane = lane_id();
@@ -1282,7 +1348,7 @@ __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) 
       if (pr > pr_last) qf.q[tt][ks] = bf16x8{};
     }
   }
-  // units this wave computes: those before its last row's limit; the first
+  // blocks this wave computes: those before its last row's limit; the first
   // n_full of them reach no row's causal limit and no position past the cache
   const int w_last = min(wr0 + 16 * QT - 1, pr_last);
   const int n_mine = has_rows ? uni(min((L + w_last / a.G + 1 + kBlk - 1) / kBlk, nb)) : 0;
@@ -1291,6 +1357,7 @@ __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) 
   floatx4 acc[QT][D / 16];
   float m_run[QT], l_run[QT];
   BlockMax<QT> ref{-INFINITY};
+  const int max_mask = win.s.nt == 1 ? 0 : a.max_mask;
   ref.reset();
 #pragma unroll
   for (int tt = 0; tt < QT; ++tt) {
@@ -1308,11 +1375,11 @@ __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) 
   const int v_off0 = v_frag_off<PS>(c16, j);
   const SkSrc<PS> src(t);
 
-  for (int n0 = 0; n0 < nb; n0 += kTileBatch) {
+  for (int n0 = nb0; n0 < nb; n0 += kTileBatch) {
     const int n1 = min(n0 + kTileBatch, nb);
     __syncthreads();                       // the batch before is done with the page ids and the ring
     for (int e = tid; e < 2 * (n1 - n0); e += 256) {
-      const int p16 = 2 * n0 + e;          // the part's place in the sequence
+      const int p16 = 2 * n0 + e;            // the part's place in the sequence
       const int page = clampi(pt_row[min(p16 / SUB, a.max_pages - 1)], 0, a.num_pages - 1);
       s_pg[e] = page * SUB + p16 % SUB;
     }
@@ -1342,7 +1409,7 @@ __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) 
       const char* buf = next_unit(n);
       if (has_rows) {
         const LdsFrags<false, kSkVStep<PS>> f{buf, k_off[0], k_off[1], v_off0, 0, 0};
-        ref.slack = ((n - 1) & a.max_mask) ? kRescaleSlack : -INFINITY;
+        ref.slack = ((n - 1) & max_mask) ? kRescaleSlack : -INFINITY;
         attend_block<bf16, D, QT, false>(a, f, qf, qlimit, kBlk * n, acc, m_run, l_run, ref);
       }
     }
@@ -1350,13 +1417,17 @@ __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) 
       const char* buf = next_unit(n);
       if (n < n_mine) {
         const LdsFrags<true, kSkVStep<PS>> f{buf, k_off[0], k_off[1], v_off0, kBlk * n + 8 * j, n_keys};
-        ref.slack = ((n - 1) & a.max_mask) ? kRescaleSlack : -INFINITY;
+        ref.slack = ((n - 1) & max_mask) ? kRescaleSlack : -INFINITY;
         attend_block<bf16, D, QT, true>(a, f, qf, qlimit, kBlk * n, acc, m_run, l_run, ref);
       }
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // reloads past the batch's end
   }
 
+  // A whole tile is written out; a piece leaves a partial.  Partials of one
+  // (sequence, head): [piece][64-row group of the window][row].
+  const int groups = (win.rows + kRows - 1) / kRows;
+  const size_t ps0 = (size_t)blockIdx.x * a.n_qg * a.max_chunks + (size_t)piece * groups;
 #pragma unroll
   for (int tt = 0; tt < QT; ++tt) {
     float l_tot = l_run[tt] + lane_xor16(l_run[tt]);
@@ -1364,15 +1435,79 @@ __global__ __launch_bounds__(256, 3) void verify_attn_tile_kernel(AttnParams a) 
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
     const int pr = wr0 + 16 * tt + c16;
     if (pr > pr_last) continue;
-    bf16* orow = reinterpret_cast<bf16*>(a.out) +
-                 ((size_t)(r0 + pr / a.G) * a.Hq + g * a.G + pr % a.G) * D;
+    if (whole) {
+      bf16* orow = reinterpret_cast<bf16*>(a.out) +
+                   ((size_t)(r0 + pr / a.G) * a.Hq + g * a.G + pr % a.G) * D;
 #pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) {
-      bf16x4 v;
+      for (int dt = 0; dt < D / 16; ++dt) {
+        bf16x4 v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = static_cast<bf16>(acc[tt][dt][e] * inv);
-      *reinterpret_cast<bf16x4*>(orow + 16 * dt + 4 * j) = v;
+        for (int e = 0; e < 4; ++e) v[e] = static_cast<bf16>(acc[tt][dt][e] * inv);
+        *reinterpret_cast<bf16x4*>(orow + 16 * dt + 4 * j) = v;
+      }
+    } else {
+      const size_t prow = ps0 * kRows + pr;
+      float* po = a.part_o + prow * D;
+#pragma unroll
+      for (int dt = 0; dt < D / 16; ++dt) *reinterpret_cast<floatx4*>(po + 16 * dt + 4 * j) = acc[tt][dt] * inv;
+      if (j == 0) a.part_lse[prow] = l_tot > 0.f ? m_run[tt] + fast_log2(l_tot) : -INFINITY;
     }
+  }
+}
+
+// One row's pieces merged, in one pass with a running maximum (each piece's
+// weight and partial are loaded together): eight channels of the row from n
+// partials, `stride` rows apart, the first at row `row`.
+__device__ __forceinline__ bf16x8 merge_pieces(const AttnParams& a, size_t row, size_t stride, int n, int dq) {
+  constexpr int D = 128;
+  float M = -INFINITY, wsum = 0.f;
+  floatx4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int w = 0; w < n; ++w) {
+    const float lse = a.part_lse[row + w * stride];
+    const float* po = a.part_o + (row + w * stride) * D + dq;
+    const floatx4 p0 = ld16<floatx4>(po), p1 = ld16<floatx4>(po + 4);
+    const float Mn = fmaxf(M, lse);
+    const float Mu = (Mn == -INFINITY) ? 0.f : Mn;
+    const float sc = fast_exp2(M - Mu);                 // 0 while M is -inf
+    const float wgt = fast_exp2(lse - Mu);
+    wsum = wsum * sc + wgt;
+    o0 = o0 * sc + wgt * p0;
+    o1 = o1 * sc + wgt * p1;
+    M = Mn;
+  }
+  const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
+  bf16x8 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    v[e] = static_cast<bf16>(o0[e] * inv);
+    v[4 + e] = static_cast<bf16>(o1[e] * inv);
+  }
+  return v;
+}
+
+// Merge the pieces of every tile that the tile kernel cut (grid: 64-row groups
+// of a window, (sequence, KV head); 16 threads per row, 8 channels each).
+__global__ __launch_bounds__(256) void attn_combine_tile_kernel(AttnParams a) {
+  constexpr int D = 128, QT = 2;
+  const int slot = blockIdx.y / a.Hkv, g = blockIdx.y % a.Hkv;
+  const int b = a.seq_ids ? a.seq_ids[slot] : slot;
+  const TileWindow win(a, b, 64 * QT);
+  const int pr0 = blockIdx.x * kRows;
+  if (pr0 >= win.rows) return;
+  const int tile = pr0 / (64 * QT);
+  const int nb = win.blocks(a, min(win.rows, (tile + 1) * 64 * QT) - 1);
+  if (nb <= win.s.cb) return;   // written whole
+  const int n = (nb + win.s.cb - 1) / win.s.cb;
+  const size_t groups = (win.rows + kRows - 1) / kRows;
+  const size_t slot0 = (size_t)blockIdx.y * a.n_qg * a.max_chunks;
+  const int dq = (threadIdx.x % 16) * (D / 16);
+  for (int r = threadIdx.x / 16; r < kRows; r += 16) {
+    const int pr = pr0 + r;
+    if (pr >= win.rows) return;
+    const bf16x8 v = merge_pieces(a, slot0 * kRows + pr, groups * kRows, n, dq);
+    *reinterpret_cast<bf16x8*>(reinterpret_cast<bf16*>(a.out) +
+                               ((size_t)(win.r0 + pr / a.G) * a.Hq + g * a.G + pr % a.G) * D + dq) = v;
   }
 }
 
@@ -1415,33 +1550,9 @@ __global__ __launch_bounds__(256) void attn_combine_sk_kernel(AttnParams a) {
   const int dq = (threadIdx.x % 16) * (D / 16);
   const int pr = qg * R + r;
   if (pr >= min(kb * G, (qg + 1) * R)) return;
-  // One pass over the pieces with a running maximum: each piece's weight and
-  // partial are loaded together.
-  float M = -INFINITY, wsum = 0.f;
-  floatx4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-  for (int w = w0; w <= w1; ++w) {
-    const float lse = a.part_lse[((size_t)it + w) * R + r];
-    const float* po = a.part_o + (((size_t)it + w) * R + r) * D + dq;
-    const floatx4 p0 = ld16<floatx4>(po), p1 = ld16<floatx4>(po + 4);
-    const float Mn = fmaxf(M, lse);
-    const float Mu = (Mn == -INFINITY) ? 0.f : Mn;
-    const float sc = fast_exp2(M - Mu);                 // 0 while M is -inf
-    const float wgt = fast_exp2(lse - Mu);
-    wsum = wsum * sc + wgt;
-    o0 = o0 * sc + wgt * p0;
-    o1 = o1 * sc + wgt * p1;
-    M = Mn;
-  }
-  const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
+  const bf16x8 v = merge_pieces(a, ((size_t)it + w0) * R + r, R, w1 - w0 + 1, dq);
   const int i = pr / G, hl = pr % G;
-  bf16x8 v;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    v[e] = static_cast<bf16>(o0[e] * inv);
-    v[4 + e] = static_cast<bf16>(o1[e] * inv);
-  }
-  *reinterpret_cast<bf16x8*>(reinterpret_cast<bf16*>(a.out) + ((size_t)(r0 + i) * a.Hq + g * G + hl) * D + dq) = v;
+  *reinterpret_cast<bf16x8*>(reinterpret_cast<bf16*>(a.out) + ((size_t)(r0 + i) * a.Hq + g * a.G + hl) * D + dq) = v;
 }
 
 // Merge the chunk partials of every (sequence, KV head, row group) that spans
@@ -1517,17 +1628,21 @@ hipError_t launch_t(const AttnParams& p, dim3 grid, dim3 cgrid, hipStream_t st) 
 }
 
 template <int PS, int QT>
-hipError_t launch_tile(const AttnParams& p, hipStream_t st) {
+hipError_t launch_tile(const AttnParams& p, int units, bool split, hipStream_t st) {
   trace_begin(st);
   hipError_t e = launch_append<bf16, 128>(p, st);
   if (e != hipSuccess) return e;
   trace_mark(st);
-  const long tiles = ((long)p.max_q * p.G + 64 * QT - 1) / (64 * QT);
-  hipLaunchKernelGGL((verify_attn_tile_kernel<PS, QT>),
-                     dim3((p.n_seq * p.Hkv + 7) / 8 * 8, (unsigned)tiles), dim3(256), 0, st, p);
+  hipLaunchKernelGGL((verify_attn_tile_kernel<PS, QT>), dim3((p.n_seq * p.Hkv + 7) / 8 * 8, units), dim3(256), 0,
+                     st, p);
   e = hipGetLastError();
+  if (e != hipSuccess) return e;
   trace_mark(st);
-  trace_mark(st);   // no combine: an empty interval
+  if (split) {
+    hipLaunchKernelGGL(attn_combine_tile_kernel, dim3(p.n_qg, p.n_seq * p.Hkv), dim3(256), 0, st, p);
+    e = hipGetLastError();
+  }
+  trace_mark(st);   // an empty interval without a combine
   return e;
 }
 
@@ -1549,6 +1664,12 @@ hipError_t launch_sk(const AttnParams& p, dim3 cgrid, hipStream_t st) {
   e = hipGetLastError();
   trace_mark(st);
   return e;
+}
+
+template <int PS>
+hipError_t launch_tiles(const AttnParams& p, const AttnPlan& pl, hipStream_t st) {
+  return pl.tile == 1 ? launch_tile<PS, 1>(p, pl.tile_units, pl.tile_split, st)
+                      : launch_tile<PS, 2>(p, pl.tile_units, pl.tile_split, st);
 }
 
 template <typename DT, int D>
@@ -1625,24 +1746,36 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
   const long share = std::max((n_it * (4 * maxblk + c4) * wmax + wden - 1) / wden, c4 + 5) + 2;
   pl.sk = D == 128 && pl.sk_grid >= 128 && n_it * (4 * maxblk + c4) < (1L << 31) &&
           2 * (n_it + 1) + 4L * n_seq + 3 * share + pl.sk_qt * n_it <= kSkMeta;
-  // Tiles without a split (verify_attn_tile_kernel), or shares of all items
-  // (stream-K).  A tile walks its keys at 0.75 us per 32-key block however
-  // many tiles there are, up to about one per compute unit; stream-K spreads
-  // every item over the chip but pays its tables, the partials and the
-  // combine (9 us where that exceeds the call itself), and every item of
-  // a window appends it again (0.03 us per window row).  By the host's bounds
-  // of keys and rows, measured on both sides of the line (us, tile / stream-K):
+  // Tiles (verify_attn_tile_kernel), or shares of all items (stream-K).  A tile
+  // walks its keys at 0.75 us per 32-key block however many tiles there are, up
+  // to about one per compute unit; stream-K spreads every item over the chip
+  // but pays its tables, the partials and the combine (9 us where that exceeds
+  // the call itself), and every item of a window appends it again (0.03 us per
+  // window row).  By the host's bounds of keys and rows, measured on both sides
+  // of the line (us, tile / stream-K):
   //   64 teacher windows of 8 rows, contexts to 300 / 1000 / 8192: 16 / 24,
-  //   29 / 37, 190 / 131; 4 of them, contexts to 1000: 25 / 20;
+  //   30 / 37, 190 / 131; 4 of them, contexts to 1000: 25 / 20;
   //   16 windows of 32 rows, contexts to 1000: 38 / 35; one prompt of 1024
-  //   teacher tokens: 41 / 92; 4 windows of 256 rows, contexts to 4096: 119 / 109.
-  // More items than the stream-K tables hold, with more than 64 rows each,
-  // fill the chip as tiles at any length (eight prompts of 512-1024 tokens:
-  // register kernel 484 us, tiles 88 us).
+  //   teacher tokens: 43 / 92; 4 windows of 256 rows, contexts to 4096: 119 / 109;
+  //   one window of 1024 rows among three of one, contexts to 5000: 64 / 113.
+  // More items than the stream-K tables hold, with more than 64 rows each, are
+  // taken as tiles at any length (us, tile / register kernel): eight prompts of
+  // 512-1024 tokens 93 / 926, the same under a table of 32K tokens 98 / 981; 16
+  // windows of 512 rows to 8000 tokens 885 / 2115; a 512-token prompt among 15
+  // one-row windows to 32K 189 / 585; 512 rows at 16K among them 1064 / 2211.
   const double fixed = 9 + 0.03 * max_q;
   if (D == 128 && (0.75 * maxblk <= fixed + 0.002 * std::min(n_it, 256L) * maxblk ||
                    (!pl.sk && n_it >= kSkGrid && rows > kRows)))
     pl.tile = pl.sk_qt;
+  const long units = tile_units((rows + 64L * pl.sk_qt - 1) / (64 * pl.sk_qt), maxblk);
+  if (units > 65535) pl.tile = 0;   // grid y
+  pl.tile_units = (int)units;
+  pl.tile_split = pl.tile == 2 && maxblk > kTileWhole;
+  // Short pieces while few (sequence, head)s share the chip, longer ones, with
+  // less to merge, where these fill it (walks of 16 / 24 / 48 blocks: four
+  // one-row windows to 5000 tokens 30 / 36 / 49 us, a prompt among 15 to 32K
+  // 213 / 203 / 183).
+  pl.tile_walk = std::clamp(n_seq * Hkv * 3 / 4, 16, 48);
   // How many of a tile's key blocks take their own maximum as reference
   // (BlockMax): about as many as one in every workgroup's share when the blocks
   // are split over the chip, so that a tile is no further from 64 bits than the
@@ -1738,6 +1871,7 @@ hipError_t launch_verify_attn(const AttnLaunch& L, const AttnPlan& pl, hipStream
   p.n_seq = L.n_seq;
   p.max_q = L.max_q;
   p.max_mask = pl.max_mask;
+  p.tile_walk = pl.tile_walk;
   const uintptr_t bases = reinterpret_cast<uintptr_t>(L.q) | reinterpret_cast<uintptr_t>(L.k_new) |
                           reinterpret_cast<uintptr_t>(L.v_new) | reinterpret_cast<uintptr_t>(L.k_cache) |
                           reinterpret_cast<uintptr_t>(L.v_cache);
@@ -1747,9 +1881,9 @@ hipError_t launch_verify_attn(const AttnLaunch& L, const AttnPlan& pl, hipStream
   dim3 cgrid(pl.n_qg, L.n_seq * L.Hkv);
   if (pl.tile && L.dtype_bf16 && L.D == 128 && p.al16) {
     switch (L.page_size) {
-      case 16: return pl.tile == 1 ? launch_tile<16, 1>(p, st) : launch_tile<16, 2>(p, st);
-      case 32: return pl.tile == 1 ? launch_tile<32, 1>(p, st) : launch_tile<32, 2>(p, st);
-      default: return pl.tile == 1 ? launch_tile<64, 1>(p, st) : launch_tile<64, 2>(p, st);
+      case 16: return launch_tiles<16>(p, pl, st);
+      case 32: return launch_tiles<32>(p, pl, st);
+      default: return launch_tiles<64>(p, pl, st);
     }
   }
   if (pl.sk && L.dtype_bf16 && L.D == 128 && (L.page_size == 16 || p.al16)) {

@@ -1,4 +1,4 @@
-"""GPU parity of verify_attn_paged on its unsplit tiles (long windows and short
+"""GPU parity of verify_attn_paged on its tiles (long windows and short
 contexts) and of the window append, against the fp64 oracle, and of the
 stream-K split on batches of the same lengths when the page table is wide."""
 import numpy as np
@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2609_36546_amd import inputs, ops
-from tests import parity
+from tests import parity, plan
 from tests.workload import to_np
 
 pytestmark = pytest.mark.gpu
@@ -47,10 +47,55 @@ def test_tiles(Hq, Hkv, ks, lo, hi, ps):
     _check(_batch(Hq, Hkv, ks, lo, hi, ps, seed=50 + ps))
 
 
+@pytest.mark.parametrize("ps", [16, 64])
+@pytest.mark.parametrize("Hq,Hkv,ks,lo,hi,B,max_q,keys", [
+    (32, 4, (1, 70, 0, 130), 1500, 2600, 4, 1500, 0),    # pieces of 16 blocks, of 80 and of 144 beside each other
+    (32, 4, (1, 5, 9), 1400, 3300, 16, 512, 32768),      # one-tile windows in longer pieces, past the stream-K tables
+    (16, 8, (1, 33, 64), 1530, 1600, 3, 900, 0),         # around the blocks that a tile walks whole
+    (8, 8, (65, 128, 129), 1500, 2100, 5, 1200, 0),      # one query head: half-filled tiles and groups
+])
+def test_tiles_cut_by_keys(Hq, Hkv, ks, lo, hi, B, max_q, keys, ps):
+    """Windows with long contexts under bounds that make the planner take the
+    tiles: their keys are cut into pieces and merged."""
+    b = _batch(Hq, Hkv, ks, lo, hi, ps, seed=65, B=B)
+    pt = _wide(b.models[0], keys // ps) if keys else None
+    p = plan.plan_of(b, b.models[0], max_q, pt)
+    assert plan.attn_kernel(p) == "tiles" and p.tile_split
+    _check(b, max_q=max_q, **({"page_table": pt} if keys else {}))
+
+
 def test_tiles_over_two_batches_of_page_ids():
-    """More than 256 key blocks per tile: the page ids are read in two batches
-    (a generous max_q makes the planner take the tiles)."""
-    _check(_batch(8, 4, (1, 5), 8150, 8300, 16, seed=61, B=3), max_q=8000)
+    """A prompt chunk whose tiles walk more than 256 key blocks: the page ids
+    are read in two batches."""
+    b = _batch(8, 4, (1, 1100), 7650, 7750, 16, seed=61, B=2)
+    assert plan.attn_kernel(plan.plan_of(b, b.models[0], 8000)) == "tiles"
+    _check(b, max_q=8000)
+
+
+def test_generous_bounds_cost_little():
+    """Sixteen one-row windows with contexts to 32K tokens: a max_q of 512
+    takes the tiles, whose walks of such contexts are cut; unsplit they took
+    4.3 times the call with the tight bound (now 1.05)."""
+    b = _batch(32, 4, (1,), 16000, 32700, 16, seed=66, B=16)
+    mdl, dev = b.models[0], b.models[0].q.device
+    ctx, cu = torch.from_numpy(b.ctx_lens).to(dev), torch.from_numpy(b.cu_q).to(dev)
+    assert plan.attn_kernel(plan.plan_of(b, mdl, 512)) == "tiles"
+    us = {}
+    for max_q in (1, 512):
+        ws = torch.empty(ops.attn_workspace_size(16, 32, 4, 128, max_q, mdl.page_table.shape[1], 16),
+                         dtype=torch.uint8, device=dev)
+        times = []
+        for _ in range(12):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            ops.verify_attn_paged(mdl.q, mdl.k_new, mdl.v_new, mdl.k_pool, mdl.v_pool, mdl.page_table, ctx, cu,
+                                  max_q=max_q, workspace=ws)
+            t1.record()
+            torch.cuda.synchronize()
+            times.append(t0.elapsed_time(t1) * 1e3)
+        us[max_q] = sorted(times)[len(times) // 2]
+    print(f"[tiles] max_q 1: {us[1]:.0f} us, 512: {us[512]:.0f} us", flush=True)
+    assert us[512] < 2 * us[1]
 
 
 @pytest.mark.parametrize("D,dtype,ps", [(64, "bf16", 32), (64, "f32", 16)])
