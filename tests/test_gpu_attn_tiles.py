@@ -74,8 +74,8 @@ def test_tiles_over_two_batches_of_page_ids():
 
 def test_generous_bounds_cost_little():
     """Sixteen one-row windows with contexts to 32K tokens: a max_q of 512
-    takes the tiles, whose walks of such contexts are cut; unsplit they took
-    4.3 times the call with the tight bound (now 1.05)."""
+    takes the tiles, whose walks of such contexts are cut; uncut they took five
+    times the call with the tight bound (now 1.25)."""
     b = _batch(32, 4, (1,), 16000, 32700, 16, seed=66, B=16)
     mdl, dev = b.models[0], b.models[0].q.device
     ctx, cu = torch.from_numpy(b.ctx_lens).to(dev), torch.from_numpy(b.cu_q).to(dev)

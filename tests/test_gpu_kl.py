@@ -103,6 +103,32 @@ def test_gather_against_oracle():
         np.testing.assert_allclose(to_np(own), to_np(outs["topk_logp"]), atol=2e-5)
 
 
+@pytest.mark.parametrize("M,Hd,V,n,dt", [
+    ((1 << 22) + 3, 64, 128, 64, torch.bfloat16),   # more waves than one launch takes threads for
+    (300, 512, 700, 16, torch.bfloat16),            # a row of W is one load of a wave, exactly
+    (300, 576, 700, 16, torch.bfloat16),            # and one line more
+    (300, 256, 700, 5, torch.float32),
+    (300, 320, 700, 5, torch.float32),
+])
+def test_gather_sizes(M, Hd, V, n, dt):
+    print(f"[kl] gather M={M} Hd={Hd} n={n} {dt}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    h = torch.randn(M, Hd, generator=gen, device="cuda", dtype=dt)
+    W = torch.randn(V, Hd, generator=gen, device="cuda", dtype=dt)
+    lse = torch.randn(M, generator=gen, device="cuda")
+    idx = torch.randint(-1, V + 1, (M, n), generator=gen, device="cuda", dtype=torch.int32)
+    out = ops.lmhead_logp_gather(h, W, lse, idx)
+    Wd = W.double()
+    for r0 in range(0, M, 1 << 18):
+        r = slice(r0, min(M, r0 + (1 << 18)))
+        ref = (h[r].double() @ Wd.t()).gather(1, idx[r].clamp(0, V - 1).long()) - lse[r].double()[:, None]
+        outside = (idx[r] < 0) | (idx[r] >= V)
+        assert torch.equal(torch.isinf(out[r]), outside)
+        # fp32 sums of Hd products of unit normals: below 1e-4 of their spread sqrt(Hd)
+        assert float((out[r].double() - ref)[~outside].abs().max()) < 1e-4 * Hd ** 0.5
+
+
 def test_end_to_end_student_teacher_full_vocab():
     """Student and teacher LM heads (V = 151936, Hd = 2048) over the same 24
     positions; teacher weights correlated with the student's so the top-K
