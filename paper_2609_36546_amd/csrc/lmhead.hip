@@ -1624,6 +1624,26 @@ void launch_stream(LmParams q, hipStream_t st) {
   hipLaunchKernelGGL(lmhead_gemm_stream_kernel<WV>, dim3((unsigned)grid), dim3(128 * WV), 0, st, q);
 }
 
+// Few rows: the stream of W, or the copied rows' 64-row tiles.  The stream
+// reads a row-major W in whole lines and needs no copy, but it has one or two
+// workgroups per compute unit whose epilogue nothing overlaps, and the tiles
+// keep more loads in flight per workgroup.  us, tiles / stream:
+//   several rounds (V > 65536): M = 16, V = 151936 Hd 64 24 / 28, 512 44 / 47,
+//   768 54 / 57; Hd 1024 row-major 75 / 70, tiled 72.5 / 72.0 (V = 262144 104 /
+//   110; M = 4, V = 151936 71 / 68); Hd 1536 tiled 105.9 / 102.4;
+//   few groups: M = 1, Hd 2048, V = 1024 39.8 / 42.5, V = 5003 36.3 / 39.4,
+//   V = 8000 35.6 / 36.6, V = 16384 36.8 / 35.9;
+//   tiled W, compute units partly filled: M = 16, Hd 4096, V = 16384 50.8 /
+//   57.6, 24000 52.0 / 57.5, 32003 61.7 / 57.9; Hd 2048, V = 50000 44.6 / 45.7,
+//   65536 45.5 / 44.9.
+bool few_rows_stream(const LmParams& p) {
+  const int cus = device_cus(), n = p.n_groups;
+  if (p.M > kSRows) return true;   // two row tiles in one round (lm_plan)
+  if (n > 2 * cus) return p.Hd >= 2048 || (p.Hd >= 1024 && (!p.w_tiled || p.M <= 8));
+  if (n <= cus / 4) return false;
+  return !p.w_tiled || 8 * n >= 7 * (n <= cus ? cus : 2 * cus);
+}
+
 template <int RB>
 void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
   // 64 * RB hidden rows per workgroup.  256 and 128 rows take eight waves
@@ -1635,9 +1655,9 @@ void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
   // copy in W's tiled block layout, written first into the workspace, so
   // that every operand load reads whole cache lines.
   // Hd is a multiple of 64 (the host checks), so of the 32-channel stage.
-  // Few rows stream W instead, reading the hidden rows in place, for which
-  // these must start on a 16-byte boundary.
-  if (RB == 1 && (reinterpret_cast<uintptr_t>(p.hidden) & 15) == 0) {
+  // Few rows stream W instead (few_rows_stream), reading the hidden rows in
+  // place, for which these must start on a 16-byte boundary.
+  if (RB == 1 && (reinterpret_cast<uintptr_t>(p.hidden) & 15) == 0 && few_rows_stream(p)) {
     trace_mark(st);   // no hidden copy: an empty interval
     // Two groups per workgroup where all the compute units get one, but for
     // the fewest rows (M = 1 120 us with one, 121 with two; M = 24 129 and
@@ -1686,7 +1706,7 @@ void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
   } else if constexpr (RB == 2)
     p.turn ? launch_dlds<4, 1, 4, 8, true>(p, st) : launch_dlds<4, 1, 4, 8>(p, st);
   else
-    launch_dlds<4, RB, 4, 4>(p, st);
+    p.turn ? launch_dlds<4, RB, 4, 4, true>(p, st) : launch_dlds<4, RB, 4, 4>(p, st);
 }
 
 template <int RB>

@@ -107,6 +107,10 @@ def test_draws_from_joined_records():
     (33, 65792 + 128, 128),   # two groups per workgroup, the last workgroup with one
     (64, 65792 + 129, 192),   # and with one group and an entry
     (64, 5003, 4096),
+    (64, 90000, 1024),        # several rounds: row-major streamed, tiled in 64-row tiles
+    (7, 90000, 512),          # several rounds of short rows: 64-row tiles
+    (5, 8192, 2048),          # few groups: 64-row tiles, sums turned
+    (20, 8193, 2048),         # row-major streamed, tiled in 64-row tiles: the same turn
     (65, 32003, 128),         # two row tiles
     (128, 2048, 2048),
 ])
@@ -119,12 +123,13 @@ def test_few_rows(M, V, Hd):
     logits = oracle.logits_fp64(to_np(h), to_np(W))
     parity.check_lmhead(g, oracle.lmhead_logsoftmax(None, None, prop, K, logits=logits), logits, K)
     t = ops.lmhead_logsoftmax_verify(h, ops.lmhead_pack_w(W), p, K)
-    # hidden rows off a 16-byte boundary take the copy and the 64-row tiles
+    # hidden rows off a 16-byte boundary take the copy and the 64-row tiles: the
+    # same order of the sums, so the same bits
     off = torch.empty(h.numel() + 4, dtype=h.dtype, device="cuda")[4:].view(h.shape)
     off.copy_(h)
     o = ops.lmhead_logsoftmax_verify(off, W, p, K)
     for key in ("lse", "logp_prop", "argmax", "topk_idx", "topk_logp", "entropy"):
-        assert torch.equal(g[key], t[key]), key
+        assert torch.equal(g[key], t[key]) and torch.equal(g[key], o[key]), key
     parity.check_lmhead(o, oracle.lmhead_logsoftmax(None, None, prop, K, logits=logits), logits, K)
 
 
