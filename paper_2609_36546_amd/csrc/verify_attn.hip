@@ -361,6 +361,7 @@ __device__ __forceinline__ void attend_block(const AttnParams& a, const FS& f,
 // 2-byte strided stores took 384 us for eight prompts of 512-1024 tokens
 // (teacher heads), latency-bound on 32 workgroups; this takes 9 us.
 constexpr int kAppend = 64;
+constexpr int kAppendFew = 4;    // rows moved without the detour through LDS (one row 2.2 us, with it 3.2)
 template <typename DT, int D>
 __global__ __launch_bounds__(256) void append_window_kernel(AttnParams a) {
   constexpr int EPL = 16 / (int)sizeof(DT);
@@ -379,6 +380,18 @@ __global__ __launch_bounds__(256) void append_window_kernel(AttnParams a) {
   DT* vc = reinterpret_cast<DT*>(a.v_cache);
   const DT* kn = reinterpret_cast<const DT*>(a.k_new);
   const DT* vn = reinterpret_cast<const DT*>(a.v_new);
+  if (kb <= kAppendFew) {                      // straight from the rows, all by the first chunk
+    if (blockIdx.x > 0) return;
+    for (int e = threadIdx.x; e < kb * D; e += 256) {
+      const int d = e % D, pos = L + e / D;
+      const int page = clampi(pt_row[clampi(pos >> a.log2ps, 0, a.max_pages - 1)], 0, a.num_pages - 1);
+      const int sl = pos & (a.page_size - 1);
+      const size_t src = ((size_t)(r0 + e / D) * a.Hkv + g) * D + d, pg = (size_t)page * a.Hkv + g;
+      kc[((pg * (D / 32) + d / 32) * a.page_size + sl) * 32 + (d & 31)] = kn[src];
+      vc[(pg * D + d) * a.page_size + sl] = vn[src];
+    }
+    return;
+  }
   __shared__ DT s_v[kAppend * LDP];
   __shared__ int s_pg[kAppend / 16];           // pages are multiples of 16 slots
   if (threadIdx.x < kAppend / 16)

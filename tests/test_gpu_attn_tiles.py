@@ -98,6 +98,13 @@ def test_generous_bounds_cost_little():
     assert us[512] < 2 * us[1]
 
 
+@pytest.mark.parametrize("D,dtype,ps", [(64, "bf16", 16), (64, "bf16", 64), (64, "f32", 32)])
+def test_append_of_few_rows(D, dtype, ps):
+    """Windows of up to four rows go straight to the pages, over page ends
+    too; five rows go through LDS."""
+    _check(_batch(4, 2, (1, 3, 4, 5, 0), 5, 150, ps, seed=67, B=40, D=D, dtype=dtype))
+
+
 @pytest.mark.parametrize("D,dtype,ps", [(64, "bf16", 32), (64, "f32", 16)])
 def test_append_of_long_windows(D, dtype, ps):
     """Windows over several 64-position chunks of the append, starting and
