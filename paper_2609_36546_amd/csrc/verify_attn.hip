@@ -87,13 +87,20 @@ struct AttnParams {
   float scale_log2;   // softmax scale * log2(e)
   int32_t* sk_start;  // stream-K: first block of every item (written by the attention kernel)
   int32_t* sk_ne;     // stream-K: non-empty items before every item (written with sk_start)
-  int sk_grid;        // stream-K: persistent workgroups
-  int item_rows;      // stream-K: packed query rows per item (64, or 128 with two tiles per wave)
-  int sk_first;       // stream-K: workgroups dispatched first on their CU (the CU count)
-  int max_q;          // bound of the handled windows' rows
-  int max_mask;       // tiles: key block n takes its own maximum as reference where (n - 1) & max_mask is 0
-  int tile_walk;      // tiles: key blocks per piece at least
-  int al16;           // the window and cache arrays start on 16-byte boundaries
+  // One place for both, since no call takes both and 16 bytes more of arguments
+  // cost the smallest calls 0.15 us.
+  union {
+    struct {
+      int sk_grid;      // stream-K: persistent workgroups
+      int item_rows;    // stream-K: packed query rows per item (64, or 128 with two tiles per wave)
+      int sk_first;     // stream-K: workgroups dispatched first on their CU (the CU count)
+    };
+    struct {
+      int max_mask;     // tiles: key block n takes its own maximum as reference where (n - 1) & max_mask is 0
+      int tile_walk;    // tiles: key blocks per piece at least
+      int al16;         // append: the window and cache arrays start on 16-byte boundaries
+    };
+  };
 };
 
 template <typename DT, int D> struct Frags;
@@ -678,13 +685,21 @@ constexpr int kSkGrid = 512;           // persistent workgroups: 2 per CU
 // Workgroups that share the B blocks of NE non-empty items.  A call with few
 // blocks is bound by latency: the blocks of a workgroup one after the other,
 // then the combine's walk over an item's pieces.  The longer the items, the
-// more blocks a workgroup takes: 3 to 8 by the mean item, up to the full grid.
-// Against one block per workgroup, us per call: 1 student row over 1500 keys
-// 18.7 -> 14.9, 3 windows of 8 teacher rows to 2912 keys 28.2 -> 19.1, one of
-// 16 student rows over 9237 keys 29.5 -> 25.1.
+// more blocks a workgroup takes, by the mean item, up to the full grid.  us per
+// call of 1, 4 or 16 windows of teacher rows (16 rows: k = 1, 64: k = 8), by
+// blocks per workgroup 1 / 2 / 3 / 4 / 5 / 8:
+//   7 blocks per item   4 x 1  12.8 13.5 14.7 15.5 16.8 19.9
+//   10                  4 x 8  15.5 14.8 15.7 16.4 17.7 20.4
+//   17                  4 x 8  18.0 16.3 16.5 17.0 17.1 19.7
+//   36                  4 x 1  17.9 16.3 15.4 16.2 16.5 18.1
+//   47                  1 x 8  18.9 16.7 16.3 16.0 16.9 18.6
+//   141                 1 x 1  28.0 21.5 19.0 18.5 17.7 18.9
+// and one window of 16 student rows, 289 blocks per item, 25.1 with 8, 29.7 with 4.
 __host__ __device__ inline int sk_workgroups(int grid, int B, int NE) {
   if (B >= 8 * grid) return grid;   // without the divisions
-  const int w = B < 24 * NE ? (B + 2) / 3 : B < 40 * NE ? (B + 3) / 4 : B < 150 * NE ? (B + 4) / 5 : (B + 7) / 8;
+  if (B < 8 * NE) return grid < B ? grid : B;
+  const int m = B < 20 * NE ? 2 : B < 40 * NE ? 3 : B < 64 * NE ? 4 : B < 150 * NE ? 5 : 8;
+  const int w = (B + m - 1) / m;
   return w < grid ? w : grid;
 }
 
@@ -783,16 +798,16 @@ __host__ __device__ constexpr int sk_item_cost(int qt) { return 16 * qt; }
 // box and shape measured) the odd-numbered XCDs streamed 6-10% slower than the
 // even ones, and a CU's second workgroup 5-10% slower than its first, which
 // ended first on almost every CU (its waves are the older ones).  Spans:
-// kSkSpan = {first even, first odd, second even, second odd}.  Only while the
-// shares average at least 8 blocks (and F is even): then no span is shorter
-// than one block's cost, so every workgroup between the first and the last
-// piece of an item holds a block of it.
+// kSkSpan = {first even, first odd, second even, second odd}.  Only where the
+// whole grid works and its shares average at least 8 blocks (and F is even):
+// then no span is shorter than one block's cost, so every workgroup between
+// the first and the last piece of an item holds a block of it.
 struct SkSpan {
   int e1, o1, e2, o2, F;
 };
 constexpr int kSkSpan[4] = {24, 22, 21, 19};
-__host__ __device__ inline SkSpan sk_spans(long blocks, int W, int first) {
-  if (blocks >= 8L * W && first > 0 && first % 2 == 0) return {kSkSpan[0], kSkSpan[1], kSkSpan[2], kSkSpan[3], first};
+__host__ __device__ inline SkSpan sk_spans(long blocks, int W, int grid, int first) {
+  if (W == grid && blocks >= 8L * W && first > 0 && first % 2 == 0) return {kSkSpan[0], kSkSpan[1], kSkSpan[2], kSkSpan[3], first};
   return {1, 1, 1, 1, 0};
 }
 __host__ __device__ inline long sk_pre(long v, int e, int o) { return e * ((v + 1) >> 1) + o * (v >> 1); }
@@ -910,9 +925,11 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
     // Share w: the blocks whose cost start lies in [y_lo, y_hi), in quarter
     // blocks (sk_item_cost), the spans weighted by XCD and CU slot (kSkSpan).
     constexpr int c4 = sk_item_cost(QT);
+    B_tot = uni(B_tot);
+    NE = uni(NE);
     W = sk_workgroups((int)gridDim.x, B_tot, NE);
     const int C = 4 * B_tot + c4 * NE;
-    const SkSpan sp = sk_spans(B_tot, W, a.sk_first);
+    const SkSpan sp = sk_spans(B_tot, W, (int)gridDim.x, a.sk_first);
     const long SW = sk_span_prefix(W, sp);
     int y_lo = 0, y_hi = 0;
     if (w < W) {
@@ -1550,7 +1567,7 @@ __global__ __launch_bounds__(256) void attn_combine_sk_kernel(AttnParams a) {
   // attention kernel's split; S the weighted span prefix).
   const int c4 = sk_item_cost(R / 64);
   const long C = 4L * B_tot + (long)c4 * NE;
-  const SkSpan sp = sk_spans(B_tot, W, a.sk_first);
+  const SkSpan sp = sk_spans(B_tot, W, a.sk_grid, a.sk_first);
   const long SW = sk_span_prefix(W, sp);
   auto wg_of = [&](int x) {
     const long cx = 4L * x + (long)c4 * (ne + 1);
@@ -1618,16 +1635,16 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnParams a) {
 }
 
 template <typename DT, int D>
-hipError_t launch_append(const AttnParams& p, hipStream_t st) {
-  const dim3 grid((unsigned)(((long)p.max_q + 15 + kAppend - 1) / kAppend), p.n_seq * p.Hkv);
+hipError_t launch_append(const AttnParams& p, int max_q, hipStream_t st) {
+  const dim3 grid((unsigned)(((long)max_q + 15 + kAppend - 1) / kAppend), p.n_seq * p.Hkv);
   hipLaunchKernelGGL((append_window_kernel<DT, D>), grid, dim3(256), 0, st, p);
   return hipGetLastError();
 }
 
 template <typename DT, int D, int QT>
-hipError_t launch_t(const AttnParams& p, dim3 grid, dim3 cgrid, hipStream_t st) {
+hipError_t launch_t(const AttnParams& p, int max_q, dim3 grid, dim3 cgrid, hipStream_t st) {
   trace_begin(st);
-  hipError_t e = launch_append<DT, D>(p, st);
+  hipError_t e = launch_append<DT, D>(p, max_q, st);
   if (e != hipSuccess) return e;
   trace_mark(st);
   hipLaunchKernelGGL((verify_attn_kernel<DT, D, QT>), grid, dim3(256), 0, st, p);
@@ -1641,9 +1658,9 @@ hipError_t launch_t(const AttnParams& p, dim3 grid, dim3 cgrid, hipStream_t st) 
 }
 
 template <int PS, int QT>
-hipError_t launch_tile(const AttnParams& p, int units, bool split, hipStream_t st) {
+hipError_t launch_tile(const AttnParams& p, int max_q, int units, bool split, hipStream_t st) {
   trace_begin(st);
-  hipError_t e = launch_append<bf16, 128>(p, st);
+  hipError_t e = launch_append<bf16, 128>(p, max_q, st);
   if (e != hipSuccess) return e;
   trace_mark(st);
   hipLaunchKernelGGL((verify_attn_tile_kernel<PS, QT>), dim3((p.n_seq * p.Hkv + 7) / 8 * 8, units), dim3(256), 0,
@@ -1680,18 +1697,18 @@ hipError_t launch_sk(const AttnParams& p, dim3 cgrid, hipStream_t st) {
 }
 
 template <int PS>
-hipError_t launch_tiles(const AttnParams& p, const AttnPlan& pl, hipStream_t st) {
-  return pl.tile == 1 ? launch_tile<PS, 1>(p, pl.tile_units, pl.tile_split, st)
-                      : launch_tile<PS, 2>(p, pl.tile_units, pl.tile_split, st);
+hipError_t launch_tiles(const AttnParams& p, int max_q, const AttnPlan& pl, hipStream_t st) {
+  return pl.tile == 1 ? launch_tile<PS, 1>(p, max_q, pl.tile_units, pl.tile_split, st)
+                      : launch_tile<PS, 2>(p, max_q, pl.tile_units, pl.tile_split, st);
 }
 
 template <typename DT, int D>
-hipError_t launch_d(const AttnParams& p, int qt, dim3 grid, dim3 cgrid, hipStream_t st) {
+hipError_t launch_d(const AttnParams& p, int max_q, int qt, dim3 grid, dim3 cgrid, hipStream_t st) {
   switch (qt) {
-    case 1: return launch_t<DT, D, 1>(p, grid, cgrid, st);
-    case 2: return launch_t<DT, D, 2>(p, grid, cgrid, st);
-    case 3: return launch_t<DT, D, 3>(p, grid, cgrid, st);
-    default: return launch_t<DT, D, 4>(p, grid, cgrid, st);
+    case 1: return launch_t<DT, D, 1>(p, max_q, grid, cgrid, st);
+    case 2: return launch_t<DT, D, 2>(p, max_q, grid, cgrid, st);
+    case 3: return launch_t<DT, D, 3>(p, max_q, grid, cgrid, st);
+    default: return launch_t<DT, D, 4>(p, max_q, grid, cgrid, st);
   }
 }
 
@@ -1755,7 +1772,8 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
   }
   const long wden = 4L * std::max(pl.sk_grid, 1) * wmin;
   // Below the full grid (sk_workgroups) a share averages m blocks and m NE / B
-  // item starts: at most 3 + 3 c4 / 4 blocks.
+  // item starts: at most 8 + c4 / 4 blocks' cost (m NE / B is at most 1 where a
+  // workgroup takes one block, 1 / 4 where it takes more), in equal spans.
   const long share = std::max((n_it * (4 * maxblk + c4) * wmax + wden - 1) / wden, c4 + 5) + 2;
   pl.sk = D == 128 && pl.sk_grid >= 128 && n_it * (4 * maxblk + c4) < (1L << 31) &&
           2 * (n_it + 1) + 4L * n_seq + 3 * share + pl.sk_qt * n_it <= kSkMeta;
@@ -1882,24 +1900,24 @@ hipError_t launch_verify_attn(const AttnLaunch& L, const AttnPlan& pl, hipStream
   p.max_chunks = pl.max_chunks;
   p.n_qg = pl.n_qg;
   p.n_seq = L.n_seq;
-  p.max_q = L.max_q;
   p.max_mask = pl.max_mask;
   p.tile_walk = pl.tile_walk;
   const uintptr_t bases = reinterpret_cast<uintptr_t>(L.q) | reinterpret_cast<uintptr_t>(L.k_new) |
                           reinterpret_cast<uintptr_t>(L.v_new) | reinterpret_cast<uintptr_t>(L.k_cache) |
                           reinterpret_cast<uintptr_t>(L.v_cache);
-  p.al16 = (bases & 15) == 0;
+  const bool al16 = (bases & 15) == 0;
+  p.al16 = al16;
   p.scale_log2 = L.scale * 1.4426950408889634f;
   dim3 grid((L.n_seq * L.Hkv + 7) / 8 * 8, pl.n_qg, pl.max_chunks);
   dim3 cgrid(pl.n_qg, L.n_seq * L.Hkv);
-  if (pl.tile && L.dtype_bf16 && L.D == 128 && p.al16) {
+  if (pl.tile && L.dtype_bf16 && L.D == 128 && al16) {
     switch (L.page_size) {
-      case 16: return launch_tiles<16>(p, pl, st);
-      case 32: return launch_tiles<32>(p, pl, st);
-      default: return launch_tiles<64>(p, pl, st);
+      case 16: return launch_tiles<16>(p, L.max_q, pl, st);
+      case 32: return launch_tiles<32>(p, L.max_q, pl, st);
+      default: return launch_tiles<64>(p, L.max_q, pl, st);
     }
   }
-  if (pl.sk && L.dtype_bf16 && L.D == 128 && (L.page_size == 16 || p.al16)) {
+  if (pl.sk && L.dtype_bf16 && L.D == 128 && (L.page_size == 16 || al16)) {
     p.part_lse = reinterpret_cast<float*>(reinterpret_cast<char*>(L.workspace) + pl.sk_o_bytes);
     p.sk_start = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(L.workspace) + pl.sk_o_bytes + pl.sk_lse_bytes);
     p.sk_ne = p.sk_start + ((size_t)L.n_seq * L.Hkv * pl.sk_n_qg + 1);
@@ -1915,10 +1933,10 @@ hipError_t launch_verify_attn(const AttnLaunch& L, const AttnPlan& pl, hipStream
     }
   }
   if (L.dtype_bf16) {
-    return L.D == 64 ? launch_d<bf16, 64>(p, pl.qt, grid, cgrid, st)
-                     : launch_d<bf16, 128>(p, pl.qt, grid, cgrid, st);
+    return L.D == 64 ? launch_d<bf16, 64>(p, L.max_q, pl.qt, grid, cgrid, st)
+                     : launch_d<bf16, 128>(p, L.max_q, pl.qt, grid, cgrid, st);
   }
-  return launch_d<float, 64>(p, pl.qt, grid, cgrid, st);   // fp32: D = 64 only
+  return launch_d<float, 64>(p, L.max_q, pl.qt, grid, cgrid, st);   // fp32: D = 64 only
 }
 
 }  // namespace ipdv

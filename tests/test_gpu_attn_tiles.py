@@ -199,3 +199,16 @@ def test_rounding_of_probabilities(Hq, Hkv, ks, lo, hi, ps, B):
             want += float(((low - exact) ** 2).sum())
     print(f"[rounding] error against the model's: {(got / want) ** 0.5:.4f}", flush=True)
     assert (got / want) ** 0.5 < 1.02
+
+
+@pytest.mark.parametrize("Hq,Hkv,k", [(32, 4, 8), (32, 4, 16), (16, 8, 1)])   # 64- and 128-row items
+@pytest.mark.parametrize("blocks", [1, 7, 8, 19, 20, 39, 40, 63, 64, 149, 150, 152, 153])
+def test_stream_k_shares_of_few_blocks(blocks, Hq, Hkv, k):
+    """One sequence of the given key blocks per item: on both sides of every
+    change of the blocks per workgroup, and shares of exactly eight blocks,
+    which keep equal spans below the full grid."""
+    L = max(0, 32 * blocks - k)
+    b = _batch(Hq, Hkv, (k,), L, L, 16, seed=68, B=1)
+    pt = _wide(b.models[0], 1024)
+    assert plan.attn_kernel(plan.plan_of(b, b.models[0], None, pt)) == "stream-k"
+    _check(b, page_table=pt)
