@@ -1760,8 +1760,12 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
   const long wmin = std::min(std::min(kSkSpan[0], kSkSpan[1]), std::min(kSkSpan[2], kSkSpan[3]));
   // Partials: one per item and workgroup boundary.  16-slot pages size the
   // workspace for the full grid; with other page sizes the workspace stays
-  // what the register kernel needs, and the grid shrinks to what it holds
-  // (below 128 workgroups the register kernel is taken).
+  // what the register kernel needs, and the grid shrinks to what it holds.
+  // The register kernel is taken below 128 workgroups, below 192 with 32-slot
+  // pages and no more than 16 rows (4 student windows of one row to 2574 keys,
+  // 158 workgroups: 17.9 us, stream-K 21.4), and where neither every item nor
+  // every compute unit gets a workgroup (24 student windows of three rows to
+  // 937 keys, 192 items, 190 workgroups: 23.4, stream-K 30.8).
   const size_t sk_rows = 64 * (size_t)pl.sk_qt;
   const size_t tables = 2 * (size_t)(n_it + 1) * sizeof(int32_t) + 256;
   pl.sk_grid = kSkGrid;
@@ -1769,13 +1773,14 @@ AttnPlan attn_plan(int n_seq, int Hq, int Hkv, int D, int max_q, int max_pages, 
     const long held = (long)((pl.workspace_bytes - std::min(pl.workspace_bytes, tables)) /
                              (sk_rows * (D + 1) * sizeof(float))) - n_it;
     pl.sk_grid = (int)std::max(0L, std::min((long)kSkGrid, held & ~1L));
+    if (pl.sk_grid < std::max(page_size == 32 && rows <= 16 ? 192L : 128L, std::min(n_it, 256L))) pl.sk_grid = 0;
   }
   const long wden = 4L * std::max(pl.sk_grid, 1) * wmin;
   // Below the full grid (sk_workgroups) a share averages m blocks and m NE / B
   // item starts: at most 8 + c4 / 4 blocks' cost (m NE / B is at most 1 where a
   // workgroup takes one block, 1 / 4 where it takes more), in equal spans.
   const long share = std::max((n_it * (4 * maxblk + c4) * wmax + wden - 1) / wden, c4 + 5) + 2;
-  pl.sk = D == 128 && pl.sk_grid >= 128 && n_it * (4 * maxblk + c4) < (1L << 31) &&
+  pl.sk = D == 128 && pl.sk_grid > 0 && n_it * (4 * maxblk + c4) < (1L << 31) &&
           2 * (n_it + 1) + 4L * n_seq + 3 * share + pl.sk_qt * n_it <= kSkMeta;
   // Tiles (verify_attn_tile_kernel), or shares of all items (stream-K).  A tile
   // walks its keys at 0.75 us per 32-key block however many tiles there are, up
