@@ -1758,12 +1758,16 @@ LmPlan lm_plan(int M, int Hd, int V, int K, bool bf16) {
   // 64*RB hidden rows per workgroup; fp32 keeps RB = 1 so that its
   // double-buffered stage fits the LDS.  bf16 above 64 rows takes the row
   // tile with the least time by rounds of one tile per compute unit (256),
-  // in us per round at Hd = 2048 (kRoundUs; the ratios hold for other Hd: the
-  // epilogue is a sixth).  One row tile of 256 or 320 rows runs its last,
-  // partial round as 128-row tiles in a second launch (launch_gemm).
+  // in us per round at Hd = 2048 (kRoundUs), where the epilogue is a sixth.  One
+  // row tile of 256 or 320 rows runs its last, partial round as 128-row tiles
+  // in a second launch (launch_gemm).
   // Measured at V = 151936 with tiles of at most 256 rows / as chosen here:
   // M = 320 318 / 239 us (two tiles of 256 did 512 rows of work), M = 384
-  // 320 / 281, M = 512 332 / 331 (256-row tiles either way).
+  // 320 / 281, M = 512 332 / 331 (256-row tiles either way); Hd = 4096, M = 320
+  // 582 / 430, M = 384 591 / 504; Hd = 1024, M = 320 195 / 157, M = 384 199 / 187.
+  // Below Hd = 1024 the epilogue weighs more, and most where half records are
+  // joined (us, 256-row tiles / 192: M = 384, V = 151936 Hd 512 117 / 120, Hd 256
+  // 91 / 98, Hd 64 75 / 86): several row tiles are of 256 or 320 rows there.
   static constexpr int kRoundUs[6] = {0, 0, 42, 54, 62, 77};
   pl.rb = 1;
   // Up to 128 rows stay with the few-row kernel (two row tiles) while one
@@ -1773,12 +1777,13 @@ LmPlan lm_plan(int M, int Hd, int V, int K, bool bf16) {
     long best = 0;
     for (int rb = 2; rb <= 5; ++rb) {
       const long n_rt = (M + 64L * rb - 1) / (64 * rb), n_vt = pl.n_vt;
+      if (Hd < 1024 && rb < 4 && n_rt > 1) continue;
       long us = (n_vt * n_rt + 255) / 256 * kRoundUs[rb];
       if (rb >= 4 && n_rt == 1) {
         const long left = n_vt % 256;
         us = n_vt / 256 * kRoundUs[rb] + (left ? (left * ((M + 127) / 128) + 255) / 256 * kRoundUs[2] + 5 : 0);
       }
-      if (rb == 2 || us < best) {
+      if (best == 0 || us < best) {
         best = us;
         pl.rb = rb;
       }

@@ -28,14 +28,15 @@ def _case(M, V, Hd, seed, dup=False):
     return h, W, prop
 
 
-@pytest.mark.parametrize("M", [129, 192, 250, 257, 320, 321, 384, 600])
+@pytest.mark.parametrize("M", [129, 192, 250, 257, 320, 321, 384, 500, 600])
 @pytest.mark.parametrize("last", [208, 64, 130])
 def test_row_tiles(M, last):
-    """192 rows (M = 129, 192: four waves; 384: eight waves, two tiles), 256
-    (250), 320 (257, 320; 600: two tiles), each with a last vocabulary tile
-    that ends inside a half group, at its end, or two entries into a group."""
+    """192 rows (M = 129, 192: four waves; 321, 384 at Hd = 1024: eight waves,
+    two tiles), 256 (250; 500: two tiles), 320 (257, 320; 600: two tiles), each with a last
+    vocabulary tile that ends inside a half group, at its end, or two entries
+    into a group."""
     V, K = FULL + last, 16
-    h, W, prop = _case(M, V, 128, M + last, dup=True)
+    h, W, prop = _case(M, V, 1024 if M in (321, 384) else 128, M + last, dup=True)
     print(f"[lmhead tiles] M={M} V={V}", flush=True)
     g = ops.lmhead_logsoftmax_verify(h, W, torch.from_numpy(prop.astype(np.int32)).cuda(), K)
     rows = np.unique(np.r_[0, 31, 32, 63, 64, 127, 128, M // 2, M - 2, M - 1, np.arange(0, M, 29)])
