@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2609_36546_amd import inputs, ops
-from tests import parity
+from tests import parity, plan
 from tests.workload import to_np
 
 pytestmark = pytest.mark.gpu
@@ -21,11 +21,11 @@ def _case(cfg, seed=0, **kw):
     return inputs.make_batch(cfg, seed=seed, device="cuda", **kw)
 
 
-def _check_all(batch, mi=0):
+def _check_all(batch, mi=0, page_table=None):
     mdl = batch.models[mi]
     seqs = to_np(mdl.seq_ids).astype(np.int64)
     D = mdl.shape.D
-    out, kc, vc = parity.run_gpu_attention(mdl, batch, seq_ids=mdl.seq_ids)
+    out, kc, vc = parity.run_gpu_attention(mdl, batch, seq_ids=mdl.seq_ids, page_table=page_table)
     ref, rkc, rvc = parity.oracle_attention(mdl, batch, seqs, D)
     rows = to_np(mdl.rows).astype(np.int64)
     worst = parity.check_attention_rows(out, ref, rows, mdl.q.dtype)
@@ -60,10 +60,9 @@ def test_long_window_two_row_groups():
 @pytest.mark.parametrize("B,ks,lo,hi,seed", [(12, (0, 1, 8, 16), 0, 300, 7),
                                               (60, (0, 4, 16), 0, 40, 8)])
 def test_empty_windows_and_row_groups(B, ks, lo, hi, seed):
-    """Teacher heads with windows of 0 rows and empty contexts in the batch: the
-    (sequence, head, row group) items with no rows, or no second row group,
-    sit between non-empty ones; with contexts of at most 40 keys there are
-    fewer key blocks than persistent workgroups."""
+    """Teacher heads with windows of 0 rows and empty contexts in the batch,
+    between others, taken as tiles (as stream-K items, under a wide page table:
+    tests/test_gpu_attn_tiles.py)."""
     cfg = inputs.scaled(inputs.WORKLOADS["teacher-bf16"], B=B, ctx_lo=lo, ctx_hi=hi, k_choices=ks,
                         models=(inputs.scaled_shape(inputs.TEACHER, vocab=512, hidden=64),))
     _check_all(_case(cfg, seed=seed))
@@ -82,19 +81,30 @@ def test_stream_k_several_row_groups(Hq, Hkv, ks, seed):
     _check_all(_case(cfg, seed=seed))
 
 
+def _wide(mdl, columns):
+    """The page table with more columns than any sequence needs (poison pages)."""
+    pt = mdl.page_table
+    pad = torch.full((pt.shape[0], columns - pt.shape[1]), mdl.poison_page, dtype=pt.dtype, device=pt.device)
+    return torch.cat([pt, pad], 1).contiguous()
+
+
 @pytest.mark.parametrize("lo,hi,seed,weighted", [(480, 540, 31, True), (400, 470, 32, False)])
 def test_stream_k_split_near_the_weight_threshold(lo, hi, seed, weighted):
     """64 teacher-head sequences whose key blocks average just above (4256)
     or just below (3660) eight per workgroup: the stream-K split weights its
     spans by XCD and CU slot only from eight blocks per share on, where its
     shortest spans still hold a block, so every workgroup between an item's
-    first and last piece has written a partial for the combine."""
+    first and last piece has written a partial for the combine.  (The page
+    table is as wide as for contexts of 2048: a tight one takes the tiles.)"""
     cfg = inputs.scaled(inputs.WORKLOADS["teacher-bf16"], B=64, ctx_lo=lo, ctx_hi=hi,
                         models=(inputs.scaled_shape(inputs.TEACHER, vocab=512, hidden=64),))
     b = _case(cfg, seed=seed)
     blocks = int(sum(-(-(int(L) + int(k)) // 32) for L, k in zip(b.ctx_lens, b.k))) * b.models[0].shape.Hkv
     assert (blocks >= 8 * 512) == weighted, blocks
-    _check_all(b)
+    pt = _wide(b.models[0], 128)
+    p = plan.plan_of(b, b.models[0], None, pt)
+    assert plan.attn_kernel(p) == "stream-k" and p.sk_grid == 512
+    _check_all(b, page_table=pt)
 
 
 @pytest.mark.parametrize("ps", [32, 64])
@@ -254,13 +264,46 @@ def test_full_size_dual_cache_teacher_sampled():
     _say(f"  full dual-cache teacher call, sequences {seqs}: worst rel err {worst:.2e}")
 
 
-def test_many_sequences_beyond_stream_k_tables():
-    """1000 teacher-head sequences: the (sequence, head) items no longer fit
-    the stream-K kernel's LDS tables, so the planner takes the register
-    kernel for full 64-row groups; both must agree with the oracle."""
+def test_many_sequences_as_tiles():
+    """1000 teacher-head sequences of at most 40 keys: 4000 workgroups of one
+    tile each, more items than the stream-K tables hold."""
     cfg = inputs.scaled(inputs.WORKLOADS["teacher-bf16"], B=1000, ctx_lo=0, ctx_hi=40, pool_tokens=None,
                         models=(inputs.scaled_shape(inputs.TEACHER, vocab=512, hidden=64),))
-    _check_all(_case(cfg, seed=11))
+    b = _case(cfg, seed=11)
+    assert plan.attn_kernel(plan.plan_of(b, b.models[0])) == "tiles"
+    _check_all(b)
+
+
+def test_many_sequences_beyond_stream_k_tables():
+    """1000 teacher-head sequences under a page table for 32K tokens: the
+    (sequence, head) items no longer fit the stream-K kernel's LDS tables, so
+    the planner takes the register kernel for full 64-row groups."""
+    cfg = inputs.scaled(inputs.WORKLOADS["teacher-bf16"], B=1000, ctx_lo=0, ctx_hi=40, pool_tokens=None,
+                        models=(inputs.scaled_shape(inputs.TEACHER, vocab=512, hidden=64),))
+    b = _case(cfg, seed=11)
+    pt = _wide(b.models[0], 2048)
+    assert plan.attn_kernel(plan.plan_of(b, b.models[0], None, pt)) == "register"
+    _check_all(b, page_table=pt)
+
+
+@pytest.mark.parametrize("ks", [(8,), (1, 3)])   # four row tiles per group, and up to two
+def test_register_kernel_chunks(ks):
+    """330 teacher-head sequences to 5000 keys under the same table: the
+    register kernel splits the longer ones into chunks of 2048 keys, which the
+    combine merges; the oracle checks sequences of one, two and three chunks."""
+    cfg = inputs.scaled(inputs.WORKLOADS["teacher-bf16"], B=330, ctx_lo=100, ctx_hi=5000, pool_tokens=None,
+                        k_choices=ks, models=(inputs.scaled_shape(inputs.TEACHER, vocab=512, hidden=64),))
+    b = _case(cfg, seed=12, poison=False)
+    mdl = b.models[0]
+    pt = _wide(mdl, 2048)
+    p = plan.plan_of(b, mdl, None, pt)
+    assert plan.attn_kernel(p) == "register" and p.chunk == 2048
+    out, _, _ = parity.run_gpu_attention(mdl, b, seq_ids=mdl.seq_ids, page_table=pt)
+    order = np.argsort(b.ctx_lens)
+    seqs = sorted({int(order[i]) for i in (0, 90, 165, 240, 329)})
+    assert {-(-(int(b.ctx_lens[q]) + 1) // 2048) for q in seqs} == {1, 2, 3}
+    ref, rows = parity.oracle_attention_subset(mdl, b, seqs, mdl.shape.D)
+    parity.check_attention_rows(out, ref, rows, mdl.q.dtype)
 
 
 def test_stream_k_shares_above_256_blocks():

@@ -44,7 +44,9 @@ def _wide(mdl, pages):
     (4, 4, (1, 16, 65), 30, 33),        # one query head per KV head, contexts around one key block
 ])
 def test_tiles(Hq, Hkv, ks, lo, hi, ps):
-    _check(_batch(Hq, Hkv, ks, lo, hi, ps, seed=50 + ps))
+    b = _batch(Hq, Hkv, ks, lo, hi, ps, seed=50 + ps)
+    assert plan.attn_kernel(plan.plan_of(b, b.models[0])) == "tiles"
+    _check(b)
 
 
 @pytest.mark.parametrize("ps", [16, 64])
@@ -140,7 +142,7 @@ def test_append_of_arrays_off_a_16_byte_boundary():
     (32, 4, (0, 1, 8, 16), 0, 300, 12, 32768),   # items without rows between others
     (32, 4, (0, 4, 16), 0, 40, 60, 32768),       # fewer key blocks than workgroups
     (32, 2, (16, 5, 0), 0, 700, 5, 32768),       # two 128-row items over the same keys
-    (16, 8, (1, 8), 480, 540, 64, 32768),        # shares around eight blocks
+    (16, 8, (1, 8), 480, 540, 64, 32768),        # the whole grid, about sixteen blocks to a share
     (16, 8, (1,), 0, 60, 1, 32768),              # a single short sequence
     (16, 8, (1, 5), 900, 2500, 4, 2100),         # larger pages: about half the grid's partials fit the workspace
 ])
@@ -148,7 +150,9 @@ def test_stream_k_with_a_wide_page_table(Hq, Hkv, ks, lo, hi, B, keys, ps):
     """Short contexts under a page table sized for long ones: the planner goes
     by the table's width, so these batches take the stream-K split."""
     b = _batch(Hq, Hkv, ks, lo, hi, ps, seed=64, B=B)
-    _check(b, page_table=_wide(b.models[0], keys // ps))
+    pt = _wide(b.models[0], keys // ps)
+    assert plan.attn_kernel(plan.plan_of(b, b.models[0], None, pt)) == "stream-k"
+    _check(b, page_table=pt)
 
 
 def _block_rounded(q, K, V, limits, scale):
@@ -167,14 +171,15 @@ def _block_rounded(q, K, V, limits, scale):
     return (low @ V / (p * w).sum((1, 2))[:, None]).to(torch.bfloat16).double(), exact
 
 
-@pytest.mark.parametrize("Hq,Hkv,ks,lo,hi,ps,B", [
-    (16, 8, (1,), 1500, 1500, 16, 1),        # stream-K, fewer workgroups than the grid: five blocks each
-    (32, 4, (8,), 700, 2900, 16, 2),         # the same, three blocks each
-    (32, 4, (5,), 1500, 2500, 64, 12),       # stream-K over 64-slot pages
-    (32, 4, (8,), 150, 900, 16, 3),          # tiles: few windows, short contexts
-    (16, 8, (200,), 0, 0, 16, 1),            # tiles: a short prompt
+@pytest.mark.parametrize("Hq,Hkv,ks,lo,hi,ps,B,kernel", [
+    (16, 8, (1,), 1500, 1500, 16, 1, "stream-k"),      # fewer workgroups than the grid: four blocks each
+    (32, 4, (8,), 700, 2900, 16, 2, "stream-k"),       # the same, three to five blocks each
+    (32, 4, (5,), 1500, 2500, 64, 12, "stream-k"),     # 64-slot pages
+    (32, 4, (8,), 700, 900, 16, 3, "stream-k"),
+    (32, 4, (8,), 150, 300, 16, 3, "tiles"),           # few windows, short contexts
+    (16, 8, (200,), 0, 0, 16, 1, "tiles"),             # a short prompt
 ])
-def test_rounding_of_probabilities(Hq, Hkv, ks, lo, hi, ps, B):
+def test_rounding_of_probabilities(Hq, Hkv, ks, lo, hi, ps, B, kernel):
     """Calls of few key blocks round each block's probabilities against the
     block's own maximum: the error against 64 bits is that of a model of this
     rounding (2% apart at most: the hardware's exp2 and fp32 scores turn a few
@@ -182,6 +187,7 @@ def test_rounding_of_probabilities(Hq, Hkv, ks, lo, hi, ps, B):
     more."""
     b = _batch(Hq, Hkv, ks, lo, hi, ps, seed=70 + B, B=B)
     mdl = b.models[0]
+    assert plan.attn_kernel(plan.plan_of(b, mdl)) == kernel
     out, kc, vc = parity.run_gpu_attention(mdl, b, seq_ids=mdl.seq_ids)
     G, D = Hq // Hkv, 128
     table = mdl.page_table.cpu().long()
