@@ -289,6 +289,13 @@ size_t ipdv_workspace_size(int which, const int32_t* host_shape_args, int n);
  * Requirements: M >= 0, Hd % 64 == 0 and Hd <= 4096, 1 <= V <= 262144,
  * 1 <= K <= min(IPDV_MAX_K, V).
  *
+ * A row's results do not depend on the other rows' values, but their last bits
+ * can depend on how many rows share the call: the order of the fp32 sums goes
+ * by M, Hd and V (for instance, above 256 rows at Hd = 2048 it is another).  A
+ * near-tie of the top-K, or a draw near an interval's end, can then fall the
+ * other way.  The same call repeats bit for bit, and both layouts of W give
+ * the same bits.
+ *
  * Errors: IPDV_EINVAL, IPDV_EUNSUPPORTED (dtype, Hd), IPDV_EWORKSPACE, IPDV_EHIP.
  */
 int lmhead_logsoftmax_verify(const void* hidden, const void* W,

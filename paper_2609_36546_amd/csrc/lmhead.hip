@@ -59,11 +59,12 @@ struct LmParams {
   // do the lines that a stage reads of all of them: workgroups that start
   // together would all ask the same channels.  With `turn` each vocabulary
   // tile starts its sum over the channels at a stage of its own.  Set for Hd a
-  // multiple of 2048 and one row tile of at most 256 rows, where W bounds the
-  // product.  Calls with a row-major W at V = 151936, Hd = 2048, us: M = 1
-  // 139 -> 120, M = 128 183 -> 166, M = 256 222 -> 202 (M = 320 256 -> 248, but
-  // 1% slower with tiled W; M = 512 336 -> 343; Hd = 1024 5% slower).  The
-  // order is the same for both layouts of W, so both give the same bits.
+  // multiple of 2048 and M at most 256, where W bounds the product.  Calls with
+  // a row-major W at V = 151936, Hd = 2048, us: M = 1 139 -> 120, M = 128 183 ->
+  // 166, M = 256 222 -> 202 (M = 320 256 -> 248, but 1% slower with tiled W; M =
+  // 512 336 -> 343; Hd = 1024 5% slower); Hd = 4096, M = 128 324 -> 308.  The
+  // order is the same for both layouts of W and in every kernel, so these give
+  // the same bits; a row scored among more than 256 has other last bits.
   int turn;
   int vt_base, n_vt_run;   // this launch's vocabulary tiles: vt_base .. vt_base + n_vt_run - 1
   // Group records, [M][rec_stride] each: the three largest logits of the group,
@@ -761,8 +762,9 @@ __global__ __launch_bounds__(64 * NW) void lmhead_gemm_dlds_kernel(LmParams p) {
 // A workgroup owns WV record groups of 128 entries and 64 rows (further rows
 // in further row tiles, next to it on its XCD), two waves per
 // group (32 rows each), three stages in LDS; one or two workgroups share a
-// compute unit.  The grid is the tile count over whole rounds, so that every
-// workgroup walks the same number of tiles.  Hidden rows are read where they
+// compute unit.  The grid is the tile count over whole rounds, so that the
+// workgroups walk equally many tiles (the last round is short of a few, and the
+// XCDs' eighths differ by one).  Hidden rows are read where they
 // are, without a copy; two groups per workgroup halve that traffic out of L2
 // (256 KB per tile at 64 rows).  Calls at V = 151936, Hd = 2048, us, the
 // kernel above with 64-row tiles / this one, row-major W, then tiled:

@@ -1253,13 +1253,14 @@ __global__ __launch_bounds__(256, 2) void verify_attn_sk_kernel(AttnParams a) {
 // takes 64 QT query rows and walks their keys: no tables, and no split, no
 // partials and no combine while the keys are few for the window's rows
 // (tile_split).  Four waves of 16 QT packed rows each share the 32-key
-// units of an LDS ring laid out as below.  QT = 2 at 159 registers and a ring
+// units of an LDS ring laid out as above.  QT = 2 at 162 registers and a ring
 // of three units keeps three workgroups on a CU; QT = 3 (221 registers, two
-// workgroups) took 96 us where this takes 88 (eight prompts of 512-1024
-// tokens, teacher heads: 0.46 PFLOP/s; the register kernel took 484), and
+// workgroups) took 96 us where this takes 89 (eight prompts of 512-1024
+// tokens, teacher heads: 0.45 PFLOP/s; the register kernel took 484), and
 // QT = 4 spills.  What bounds it is the chain within a unit (scores, row
 // maximum, exponentials, second product), of which three waves per SIMD hide
-// a part.  Rows of a wave are neighbours: near the causal edge a wave skips
+// a part: the matrix cores are busy for 29% of the time, waves wait to issue
+// for 36% of theirs.  Rows of a wave are neighbours: near the causal edge a wave skips
 // the units past its last row.
 //
 // The host knows bounds, not windows: one long window, or a generous max_q,
