@@ -1759,7 +1759,8 @@ LmPlan lm_plan(int M, int Hd, int V, int K, bool bf16) {
   pl.n_vt = (V + kVT - 1) / kVT;
   // 64*RB hidden rows per workgroup; fp32 keeps RB = 1 so that its
   // double-buffered stage fits the LDS.  bf16 above 64 rows takes the row
-  // tile with the least time by rounds of one tile per compute unit (256),
+  // tile with the least time by rounds of one tile per compute unit (256: the
+  // workspace query plans too, and has no device to ask),
   // in us per round at Hd = 2048 (kRoundUs), where the epilogue is a sixth.  One
   // row tile of 256 or 320 rows runs its last, partial round as 128-row tiles
   // in a second launch (launch_gemm).
