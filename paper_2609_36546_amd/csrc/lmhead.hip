@@ -1714,7 +1714,9 @@ void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, bf16) {
 template <int RB>
 void launch_gemm(const LmParams& p, dim3 grid, hipStream_t st, float) {
   trace_mark(st);   // no hidden copy for fp32: an empty interval
-  // Few tiles leave most compute units idle: split them further.
+  // Few tiles leave most compute units idle: split them further.  Whole calls at
+  // the line, 64 tiles, staged / split, us: 64 rows, V = 16384, Hd 64 19.5 / 17.8,
+  // 1024 88 / 43, 4096 308 / 117; 4096 rows, V = 256, Hd 256 365 / 206.
   if (p.n_vt * p.n_rt <= 64) {
     hipLaunchKernelGGL(lmhead_gemm_f32_split_kernel, dim3(p.n_groups, (p.M + 31) / 32), dim3(256), 0, st, p);
     return;
